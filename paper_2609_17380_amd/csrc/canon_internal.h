@@ -23,7 +23,6 @@ struct GemmArgs {
   int64_t sa1, sa2, sb1, sb2, sc1, sc2;
   int64_t nb2, batch;
   int32_t trans_a, trans_b, out_bf16, kmode, tri_lower;
-  int32_t vec;      // set by the launcher: 16-byte operand loads allowed
   int32_t b_group;  // > 1: B's inner batch offset is (z2 / b_group) * sb2 (grouped key/value heads)
   int64_t kwin;     // > 0: sliding attention window for the KMODE ranges and the tri_lower band
   int32_t zero_dead;  // EPI_DS with tri_lower: write the +0 of every tile without a visible entry (0: only
