@@ -47,6 +47,10 @@ struct GemmArgs {
 enum { EPI_NONE = 0, EPI_DS = 1, EPI_ACCUM = 2, EPI_RES = 3 };
 
 hipError_t gemm_launch(const GemmArgs& g, hipStream_t s);
+int64_t device_cus();  // compute units of the current device
+// gemm_split.hip: outputs too small to fill the chip, K split over wavefronts
+int gemm_split_config(const GemmArgs& g, int64_t cus);  // 16 * row groups + K blocks, or 0: the general kernel
+hipError_t gemm_split_launch(const GemmArgs& g, int cfg, hipStream_t s);
 
 // gemm_i8.hip: exact int8 GEMM (a [m][k], b [n][k]) with optional int32 and dequantised fp32 outputs
 struct GemmI8Args {

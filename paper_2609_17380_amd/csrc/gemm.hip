@@ -872,11 +872,7 @@ __global__ __launch_bounds__(256, 2) void gemm_short_kernel(GemmArgs g) {
 
 // g: A [m][k] and B [n][k] (both k-contiguous), 1 <= chunks <= 4
 static hipError_t launch_short(const GemmArgs& g, int64_t nc, int64_t tiles, hipStream_t s) {
-  int dev = 0, cus = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return e;
-  int64_t want = 2 * (int64_t)(cus > 0 ? cus : 1);  // two resident workgroups per CU
+  int64_t want = 2 * device_cus();                  // two resident workgroups per CU
   if (want >= 8) want -= want % 8;                  // whole groups of the 8 XCDs
   const dim3 grid((unsigned)(tiles < want ? tiles : want));
   if (nc == 1) hipLaunchKernelGGL((gemm_short_kernel<false, true, 1>), grid, dim3(256), 0, s, g);
@@ -894,7 +890,9 @@ static hipError_t launch_short(const GemmArgs& g, int64_t nc, int64_t tiles, hip
 //   three register fold levels, 0-3% faster than the 32x32 shape; left k-major, its 4-byte LDS reads per
 //   product (twice as many as with the 32x32 instruction) made it 2-18% slower.
 // * Only B k-major (input gradients): 64 x 128 tiles of the 32x32 instruction, two per CU; the transposed
-//   16x16 shape was 0-6% slower there.
+//   16x16 shape was 0-6% slower there.  With fewer than two such tiles per CU (causal launches apart) the 64 x 64
+//   shape fills the chip better: 1536 x 2048 x 4096 in TFLOP/s 81 against 104, 1024 x 1024 x 4096 48 against 80;
+//   at two per CU (2048 x 2048) they tie.
 typedef GemmCfg<16, 1, 3, 4, 4> CfgRowRow;
 typedef GemmCfg<16, 1, 3, 4, 3, true> CfgAKMajor;
 typedef GemmCfg<32, 2, 2, 3, 2> CfgBKMajor;
@@ -905,7 +903,7 @@ static dim3 general_grid(const GemmArgs& g) {
 }
 
 template <int MAXL>
-static hipError_t launch_maxl(const GemmArgs& g, hipStream_t s) {
+static hipError_t launch_maxl(const GemmArgs& g, int64_t cus, hipStream_t s) {
   typedef CfgRowRow R;
   typedef CfgAKMajor A;
   typedef CfgBKMajor B;
@@ -920,8 +918,11 @@ static hipError_t launch_maxl(const GemmArgs& g, hipStream_t s) {
       hipLaunchKernelGGL((gemm_mfma_kernel<MAXL, true, true, A, true>), general_grid<A>(g), dim3(A::NT), 0, s, g);
     return hipGetLastError();
   }
+  const int64_t tilesB = ((g.m + BM - 1) / BM) * ((g.n + B::TBN - 1) / B::TBN) * g.batch;
   if (!g.trans_a && g.trans_b)
     hipLaunchKernelGGL((gemm_mfma_kernel<MAXL, false, true, R, false>), general_grid<R>(g), dim3(R::NT), 0, s, g);
+  else if (!g.trans_a && !g.trans_b && tilesB < 2 * cus)
+    hipLaunchKernelGGL((gemm_mfma_kernel<MAXL, false, false, A, false>), general_grid<A>(g), dim3(A::NT), 0, s, g);
   else if (!g.trans_a && !g.trans_b)
     hipLaunchKernelGGL((gemm_mfma_kernel<MAXL, false, false, B, false>), general_grid<B>(g), dim3(B::NT), 0, s, g);
   else if (g.trans_a && !g.trans_b)
@@ -933,8 +934,19 @@ static hipError_t launch_maxl(const GemmArgs& g, hipStream_t s) {
 
 int gemm_max_levels() { return 12; }
 
+int64_t device_cus() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+    cus = 256;
+  return cus;
+}
+
 hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
   if (g.m == 0 || g.n == 0 || g.batch == 0) return hipSuccess;
+  const int64_t cus = device_cus();
+  const int cfg = gemm_split_config(g, cus);
+  if (cfg) return gemm_split_launch(g, cfg, s);
   const int64_t nc = (g.k + KC - 1) / KC;
   int bits = 0;
   while ((int64_t(1) << bits) <= nc) ++bits;  // nc < 2^bits: a push never runs past the top level
@@ -944,12 +956,12 @@ hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
       BM * g.ldc < (int64_t(1) << 31) && BM * g.ds_ldp < (int64_t(1) << 31) && tiles * g.batch < (int64_t(1) << 31) &&
       g.nb2 > 0 && g.batch % g.nb2 == 0)
     return launch_short(g, nc, tiles * g.batch, s);
-  if (bits <= 3) return launch_maxl<3>(g, s);
-  if (bits <= 5) return launch_maxl<5>(g, s);
-  if (bits <= 7) return launch_maxl<7>(g, s);
-  if (bits <= 9) return launch_maxl<9>(g, s);
-  if (bits <= 11) return launch_maxl<11>(g, s);
-  if (bits <= 12) return launch_maxl<12>(g, s);
+  if (bits <= 3) return launch_maxl<3>(g, cus, s);
+  if (bits <= 5) return launch_maxl<5>(g, cus, s);
+  if (bits <= 7) return launch_maxl<7>(g, cus, s);
+  if (bits <= 9) return launch_maxl<9>(g, cus, s);
+  if (bits <= 11) return launch_maxl<11>(g, cus, s);
+  if (bits <= 12) return launch_maxl<12>(g, cus, s);
   return hipErrorInvalidValue;
 }
 
