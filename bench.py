@@ -28,7 +28,8 @@ PEAK_HBM = 8000.0        # GB/s
 PEAK_INT8_MFMA = 5000.0  # TOP/s, MI355X dense int8 matrix
 PEAK_VALU_OPS = 78.6     # T lane-operations/s: 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz (the fp32 vector rate, 157.3
                          # TFLOP/s counting an FMA as 2; counters show kernels issuing above a 16-lane rate)
-SHA_BLOCK_VALU = 1698    # VALU instructions of one SHA-256 compression in hash_leaves_kernel's block loop (gfx950 ISA)
+SHA_BLOCK_VALU = 1448    # VALU instructions of one SHA-256 compression in hash_leaves_kernel's block loops (rounds 903,
+                         # schedule 545; gfx950 ISA)
 
 L, D, H, HD, F, V, S, MB = 16, 2048, 16, 128, 8192, 50304, 2048, 4
 PLAN = (1, 8, 1)

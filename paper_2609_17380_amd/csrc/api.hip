@@ -673,24 +673,25 @@ float* plan_cursor_finish(canon_plan_cursor* c, float* base, float* out, hipStre
 }
 
 struct HashPlan {
-  int64_t total_leaves = 0, n_wg = 0;
-  size_t off_tens = 0, off_wgt = 0, off_wgf = 0, off_la = 0, off_lb = 0, off_td = 0, bytes = 0;
+  int64_t group = 0, n_wg = 0;  // leaves per group; leaf groups: workgroups of the leaf pass, and the nodes they leave
+  size_t off_tens = 0, off_wgt = 0, off_wgf = 0, off_na = 0, off_nb = 0, off_td = 0, bytes = 0;
 };
 
 HashPlan hash_plan(int64_t n, const int64_t* nbytes) {
   HashPlan hp;
+  int64_t leaves = 0;
+  for (int64_t t = 0; t < n; ++t) leaves += hash_leaf_count(nbytes[t]);
+  hp.group = hash_leaf_group(leaves);
   for (int64_t t = 0; t < n; ++t) {
-    const int64_t w = hash_leaf_count(nbytes[t]);
-    hp.total_leaves += w;
-    hp.n_wg += (w + 255) / 256;
+    hp.n_wg += (hash_leaf_count(nbytes[t]) + hp.group - 1) / hp.group;
   }
   auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
   size_t o = 0;
   hp.off_tens = o; o += up(sizeof(HashTensor) * (size_t)n);
   hp.off_wgt = o; o += up(sizeof(int32_t) * (size_t)hp.n_wg);
   hp.off_wgf = o; o += up(sizeof(int64_t) * (size_t)hp.n_wg);
-  hp.off_la = o; o += up(32 * (size_t)hp.total_leaves);
-  hp.off_lb = o; o += up(32 * (size_t)hp.total_leaves);
+  hp.off_na = o; o += up(32 * (size_t)hp.n_wg);
+  hp.off_nb = o; o += up(32 * (size_t)hp.n_wg);
   hp.off_td = o; o += up(32 * (size_t)n);
   hp.bytes = o;
   return hp;
@@ -715,33 +716,31 @@ canon_status state_hash_enqueue(int64_t n_tensors, const void* const* ptrs, cons
   if (workspace_bytes < hp.bytes) return CANON_EWORKSPACE;
   if (hp.n_wg > INT32_MAX) return CANON_EUNSUPPORTED;
   // host tables: per tensor, and per workgroup (tensor, first leaf)
-  std::vector<char> host(hp.off_la);
+  std::vector<char> host(hp.off_na);
   HashTensor* tens = (HashTensor*)(host.data() + hp.off_tens);
   int32_t* wgt = (int32_t*)(host.data() + hp.off_wgt);
   int64_t* wgf = (int64_t*)(host.data() + hp.off_wgf);
-  int64_t leaf = 0, wg = 0;
+  int64_t wg = 0;
   for (int64_t t = 0; t < n_tensors; ++t) {
     const int64_t w = hash_leaf_count(nbytes[t]);
     tens[t].ptr = ptrs[t];
     tens[t].nbytes = nbytes[t];
     tens[t].leaves = w;
-    tens[t].leaf_offset = leaf;
-    tens[t].aligned = (((uintptr_t)ptrs[t]) & 15) == 0;
-    for (int64_t f = 0; f < w; f += 256) {
+    tens[t].node_offset = wg;
+    for (int64_t f = 0; f < w; f += hp.group) {
       wgt[wg] = (int32_t)t;
       wgf[wg] = f;
       ++wg;
     }
-    leaf += w;
   }
   char* ws = (char*)workspace;
-  if (hp.off_la > 0) {
-    hipError_t e = hipMemcpyAsync(ws, host.data(), hp.off_la, hipMemcpyHostToDevice, s);
+  if (hp.off_na > 0) {
+    hipError_t e = hipMemcpyAsync(ws, host.data(), hp.off_na, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return CANON_EDEVICE;
   }
-  return dev(hash_launch(n_tensors, (const HashTensor*)(ws + hp.off_tens), hp.n_wg,
+  return dev(hash_launch(n_tensors, (const HashTensor*)(ws + hp.off_tens), hp.group, hp.n_wg,
                          (const int32_t*)(ws + hp.off_wgt), (const int64_t*)(ws + hp.off_wgf),
-                         (uint32_t*)(ws + hp.off_la), (uint32_t*)(ws + hp.off_lb), (uint32_t*)(ws + hp.off_td),
+                         (uint32_t*)(ws + hp.off_na), (uint32_t*)(ws + hp.off_nb), (uint32_t*)(ws + hp.off_td),
                          digest, s));
 }
 

@@ -69,13 +69,13 @@ hipError_t gemm_i8_launch(const GemmI8Args& g, hipStream_t s);
 // hash.hip: canonical state hash
 struct HashTensor {
   const void* ptr;
-  int64_t nbytes, leaves, leaf_offset;
-  int32_t aligned;  // 16-byte aligned base: vector loads
+  int64_t nbytes, leaves, node_offset;  // node_offset: its first slot among the leaf groups' nodes
 };
 int64_t hash_leaf_count(int64_t nbytes);
-hipError_t hash_launch(int64_t n_tensors, const HashTensor* tens_dev, int64_t n_wg, const int32_t* wg_tensor,
-                       const int64_t* wg_first, uint32_t* leaf_a, uint32_t* leaf_b, uint32_t* tensor_digests,
-                       uint8_t* out, hipStream_t s);
+int64_t hash_leaf_group(int64_t total_leaves);  // leaves per workgroup, folded to one node
+hipError_t hash_launch(int64_t n_tensors, const HashTensor* tens_dev, int64_t group, int64_t n_wg,
+                       const int32_t* wg_tensor, const int64_t* wg_first, uint32_t* node_a, uint32_t* node_b,
+                       uint32_t* tensor_digests, uint8_t* out, hipStream_t s);
 
 // qlinear.hip: int8 backward (rotated straight-through gradients); dy fp32, or bf16 when dy_bf16
 size_t qlinear_bwd_workspace_bytes(int64_t T, int64_t N, int64_t K);

@@ -43,3 +43,26 @@ def test_model_state_and_sensitivity():
     assert d == H.state_digest([host_bytes(t) for t in tensors])
     tensors[3].view(-1)[5] += 1  # one value of one tensor changes
     assert device_digest(tensors) != d
+
+
+def test_tree_shapes():
+    # leaves per tensor around the groups folded inside one workgroup (64 leaves of 64 KB), odd counts on every level,
+    # partial last blocks whose padding takes one and two blocks
+    rng = np.random.default_rng(4)
+    leaf = 64 * 1024
+    sizes = [leaf * 2 + 1, leaf * 63 + 55, leaf * 64, leaf * 64 + 56, leaf * 65 + 64, leaf * 129 - 1, leaf * 193 + 119]
+    ts = [torch.from_numpy(rng.integers(0, 256, n, dtype=np.uint8)).to(DEV) for n in sizes]
+    print("state hash tree shapes", sizes, flush=True)
+    assert device_digest(ts) == H.state_digest([host_bytes(t) for t in ts])
+
+
+def test_large_state_takes_the_wide_groups():
+    # 98304 leaves and more in all (one 105 MB tensor, 62 times): workgroups of 256 leaves
+    n, times = 64 * 1024 * 1600 + 57, 62
+    t = torch.from_numpy(np.random.default_rng(5).integers(0, 256, n, dtype=np.uint8)).to(DEV)
+    print("state hash of", n, "bytes,", times, "times", flush=True)
+    assert H.leaf_count(n) * times >= 98304
+    root = H.merkle_root(H.leaf_digests(host_bytes(t)))
+    want = H.sha256(b"\x03" + b"".join(H.sha256(b"\x02" + i.to_bytes(8, "little") + n.to_bytes(8, "little") + root)
+                                       for i in range(times)))
+    assert device_digest([t] * times) == want
