@@ -41,14 +41,15 @@ constexpr float kInvFact5 = 0x1.111112p-7f;     // RN32(1/5!)                0x3
 constexpr float kInvFact6 = 0x1.6c16c2p-10f;    // RN32(1/6!)                0x3AB60B61
 constexpr float kInvFact7 = 0x1.a01a02p-13f;    // RN32(1/7!)                0x39500D01
 
-__device__ __forceinline__ float cexp(float x) {
-  // written without branches (the range checks select the result), so unrolled loops of cexp stay
-  // straight-line code; the arithmetic is the same sequence of roundings either way
-  float t = x * kLog2e;
-  float kf = __builtin_rintf(t);  // nearest integer, ties to even
-  float hi = kf * kLn2Hi;
-  float lo = kf * kLn2Lo;
-  float r = x - hi;
+// t = RN(x * log2 e) and the polynomial part p and scale 2^k of cexp.  k = rne(t) comes from adding 1.5 2^23 (exact
+// rounding to an integer for |t| < 2^22; a larger |t| is selected away by the callers), whose sum also holds k in its
+// low bits; k LN2_HI is exact, so one fused operation gives RN(x - RN(k LN2_HI)).
+__device__ __forceinline__ float cexp_parts(float x, float& t, float& scale) {
+  t = x * kLog2e;
+  const float u = t + 0x1.8p23f;
+  const float kf = u - 0x1.8p23f;
+  float r = __builtin_fmaf(-kf, kLn2Hi, x);
+  const float lo = kf * kLn2Lo;
   r = r - lo;
   float p = kInvFact7;
   p = p * r; p = p + kInvFact6;
@@ -58,13 +59,41 @@ __device__ __forceinline__ float cexp(float x) {
   p = p * r; p = p + kInvFact2;
   p = p * r; p = p + 1.0f;
   p = p * r; p = p + 1.0f;
-  const float kc = fminf(fmaxf(kf, -126.0f), 127.0f);  // k itself whenever the result is not selected away
-  const int k = (int)kc;
-  float scale = __uint_as_float((uint32_t)(k + 127) << 23);
+  scale = __uint_as_float((__float_as_uint(u) << 23) + 0x3F800000u);  // 2^k for -126 <= k <= 127
+  return p;
+}
+
+__device__ __forceinline__ float cexp(float x) {
+  // written without branches (the range checks select the result), so unrolled loops of cexp stay
+  // straight-line code.  k < -125 iff t <= -125.5 and k > 127 iff t >= 127.5 (ties to even).
+  float t, scale;
+  const float p = cexp_parts(x, t, scale);
   float res = p * scale;
-  res = (kf < -125.0f) ? 0.0f : res;
-  res = (kf > 127.0f) ? __builtin_inff() : res;
+  res = (t <= -125.5f) ? 0.0f : res;
+  res = (t >= 127.5f) ? __builtin_inff() : res;
   return res;
+}
+
+// cexp of x <= 0 (or NaN), the arguments of the row softmaxes: no overflow select
+__device__ __forceinline__ float cexp_neg(float x) {
+  float t, scale;
+  const float p = cexp_parts(x, t, scale);
+  const float res = p * scale;
+  return (t <= -125.5f) ? 0.0f : res;
+}
+// cexp where RN(x * log2 e) > -125.5 is known as well (or x is NaN): no select at all
+__device__ __forceinline__ float cexp_mid(float x) {
+  float t, scale;
+  const float p = cexp_parts(x, t, scale);
+  return p * scale;
+}
+__device__ __forceinline__ bool cexp_is_mid(float x) { return x * kLog2e > -125.5f; }
+
+// two finite or infinite, never subnormal values (results of arithmetic: flushed) to bf16, round to nearest even
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  uint32_t r;
+  asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(lo), "v"(hi));
+  return r;
 }
 
 // ---- clog: x = 2^e f, f in (sqrt(1/2), sqrt(2)]; s = (f-1)/(f+1); log f = 2 atanh(s) by the odd series

@@ -53,15 +53,6 @@ __device__ __forceinline__ void ldb(const uint16_t* p, float (&f)[W]) {
   }
 }
 
-__device__ __forceinline__ void ldb8_regs(const uint4& u, float (&f)[8]) {
-  const uint32_t w4[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    f[2 * i] = bf16_to_f32((uint16_t)(w4[i] & 0xFFFFu));
-    f[2 * i + 1] = bf16_to_f32((uint16_t)(w4[i] >> 16));
-  }
-}
-
 template <int W>
 __device__ __forceinline__ void stb(uint16_t* p, const uint16_t (&h)[W]) {
   if constexpr (W == 1) {
@@ -639,7 +630,7 @@ __global__ __launch_bounds__(256) void softmax_causal_kernel(int64_t rows, int64
       float e = 0.0f;
       if ((j + t <= i && j + t >= j0)) {
         float sc = v[t] * scale;
-        e = cexp(sc - m);
+        e = cexp_neg(sc - m);
       }
       f[t] = e;
     }
@@ -657,7 +648,7 @@ __global__ __launch_bounds__(256) void softmax_causal_kernel(int64_t rows, int64
         o[t] = 0;
         if ((j + t <= i && j + t >= j0)) {
           float sc = v[t] * scale;
-          float e = cexp(sc - m);
+          float e = cexp_neg(sc - m);
           o[t] = f32_to_bf16(e * rcp);
         }
       }
@@ -706,7 +697,7 @@ __global__ __launch_bounds__(256) void softmax_causal_reg_kernel(int64_t rows, i
       float x = 0.0f;
       if (j < cols && j <= i && j >= j0) {
         float sc = e[q][t] * scale;
-        x = cexp(sc - m);
+        x = cexp_neg(sc - m);
       }
       e[q][t] = x;
     }
@@ -773,7 +764,7 @@ __global__ __launch_bounds__(256) void softmax_causal_reg2_kernel(int64_t rows, 
       float x = 0.0f;
       if (j < ncol && j <= i && j >= j0) {
         float sc = e[q][t] * scale;
-        x = cexp(sc - m);
+        x = cexp_neg(sc - m);
       }
       e[q][t] = x;
     }
@@ -862,7 +853,7 @@ __global__ __launch_bounds__(256) void softmax_band_kernel(int64_t rows, int64_t
       float x = 0.0f;
       if (seen(base + 256 * q + 4 * lane + t)) {
         float sc = e[q][t] * scale;
-        x = cexp(sc - m);
+        x = cexp_neg(sc - m);
       }
       e[q][t] = x;
     }
@@ -927,157 +918,147 @@ hipError_t softmax_causal_launch(int64_t rows, int64_t cols, const float* raw, f
 }
 
 // ------------------------------------------------------------------------------------------------
-// Cross-entropy: one 256-thread workgroup per row.  The four wavefronts take the row's 2048-term segments
-// round-robin and write the chunk partials; the partials are then folded across the workgroup.  With W = 8
-// (vocab a multiple of 8, 16-byte aligned logits and dlogits) every logit load and dlogit store moves 8 bf16
-// values per lane.  parts[] is dynamic LDS sized to the row's chunk count.
-
-template <int W>
-__global__ __launch_bounds__(256) void xent_kernel(int64_t rows, int64_t vocab, const uint16_t* __restrict__ logits,
-                                                   const int32_t* __restrict__ targets, float inv_tokens,
-                                                   float z_loss, float z2, uint16_t* __restrict__ dlogits,
-                                                   float* __restrict__ row_loss) {
-  __shared__ WaveStage st[4];
-  extern __shared__ float parts[];
-  __shared__ float red[4];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t row = blockIdx.x;
-  const uint16_t* lr = logits + row * vocab;
-  float m = -__builtin_inff();
-  for (int64_t j = (int64_t)threadIdx.x * W; j < vocab; j += 256 * W) {
-    float f[W];
-    ldb<W>(lr + j, f);
+// Cross-entropy, one workgroup of NT threads per row, the row read from memory once: thread t holds the 8 logits
+// 8 (t + NT q) .. + 7 for q < Q.  EXPS keeps the exponentials in registers (one cexp per logit, rows up to 26624);
+// longer rows keep the bf16 logits in 64 or 108 registers, so that two (one) workgroups of 16 wavefronts share a CU,
+// and evaluate cexp again for the output (50304 logits with the exponentials kept: 512 threads 584 us, 1024 threads,
+// one workgroup per CU, 543; logits kept: 531).  The exponentials are staged SEG vectors at a time as chunk rows of 36
+// floats (16-byte stores, and 16-byte reads without bank conflicts), thread c running chunk c's chain.  Rows start at
+// any element (16-byte accesses need no alignment).
+// Bound: vector instructions, about 56 per logit with two cexp of 22 (no range selects where no logit is far enough
+// below the maximum).  8192 x 50304: 750 -> 531 us (3.1 TB/s); 8192 x 50257: 2010 -> 592; 8192 x 20000: 402 -> 206.
+struct __attribute__((packed, aligned(2))) Row8 {
+  uint32_t w[4];
+};
+__device__ __forceinline__ void widen_row8(const Row8& u, float (&f)[8]) {  // a subnormal is flushed by its first use
 #pragma unroll
-    for (int i = 0; i < W; ++i) m = fmaxf(m, f[i]);
-  }
-  m = wave_max(m);
-  if (lane == 0) red[w] = m;
-  __syncthreads();
-  m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  for (int64_t seg0 = (int64_t)w * 64 * kChunk; seg0 < vocab; seg0 += 4 * 64 * kChunk)
-    wave_segment_chunks<W>(seg0, vocab, st[w], parts, [&](int64_t j, float (&f)[W]) {
-      ldb<W>(lr + j, f);
-#pragma unroll
-      for (int i = 0; i < W; ++i) f[i] = cexp(f[i] - m);
-    });
-  __syncthreads();
-  const int64_t nc = (vocab + kChunk - 1) / kChunk;
-  const int64_t G = block_chunks(nc, 256);
-  const int64_t c0 = threadIdx.x * G, c1 = (c0 + G < nc) ? c0 + G : nc;
-  LocalFold f;
-  for (int64_t c = c0; c < c1; ++c) f.push(parts[c]);
-  const float S = block_fold(f.result(), (nc + G - 1) / G);
-  const int32_t y = targets[row];
-  const bool valid = y >= 0 && y < vocab;
-  // z-loss (weight z_loss, z2 = RN(2 z_loss)): the row loss gains RN(z_loss * RN(lse^2)) and every
-  // probability is scaled by RN(1 + RN(z2 * lse)) before the target is subtracted
-  const float lse = m + clog(S);
-  const bool zl = z_loss != 0.0f;
-  const float zt = z2 * lse;
-  const float pscale = 1.0f + zt;
-  if (threadIdx.x == 0) {
-    float ce = lse - bf16_to_f32(lr[valid ? y : 0]);
-    if (zl) {
-      const float l2 = lse * lse;
-      const float zterm = z_loss * l2;
-      ce = ce + zterm;
-    }
-    row_loss[row] = valid ? ce : __builtin_nanf("");
-  }
-  const float rcp = 1.0f / S;
-  if (dlogits) {
-    for (int64_t j = (int64_t)threadIdx.x * W; j < vocab; j += 256 * W) {
-      float fv[W];
-      uint16_t h[W];
-      ldb<W>(lr + j, fv);
-#pragma unroll
-      for (int i = 0; i < W; ++i) {
-        float e = cexp(fv[i] - m);
-        float pr = e * rcp;
-        if (zl) pr = pr * pscale;
-        float q = pr - ((j + i) == y ? 1.0f : 0.0f);
-        h[i] = f32_to_bf16(q * inv_tokens);
-      }
-      stb<W>(dlogits + row * vocab + j, h);
-    }
+  for (int i = 0; i < 4; ++i) {
+    f[2 * i] = __uint_as_float(u.w[i] << 16);
+    f[2 * i + 1] = __uint_as_float(u.w[i] & 0xFFFF0000u);
   }
 }
 
-// Cross-entropy with the row's bf16 logits held in registers (vocab <= 51200, a multiple of 8, aligned):
-// thread t holds elements 8 (t + 256 q) .. +7 for q < kXentQ, read once.  Segment s of 2048 terms is
-// exactly vector q = s of every thread, so the workgroup stages four segments at a time (one per
-// wavefront buffer, thread t writing chunk t/4 at offset 8 (t % 4)), then wavefront w runs the chains of
-// segment buffer w.
-constexpr int kXentQ = 25;
-constexpr int64_t kXentRegVocab = 256 * 8 * kXentQ;
-
-__global__ __launch_bounds__(256) void xent_reg_kernel(int64_t rows, int64_t vocab,
-                                                       const uint16_t* __restrict__ logits,
-                                                       const int32_t* __restrict__ targets, float inv_tokens,
-                                                       float z_loss, float z2, uint16_t* __restrict__ dlogits,
-                                                       float* __restrict__ row_loss) {
-  __shared__ WaveStage st[4];
+template <int NT, int Q, bool EXPS>
+__global__ __launch_bounds__(NT) void xent_row_kernel(int vocab, const uint16_t* __restrict__ logits,
+                                                      const int32_t* __restrict__ targets, float inv_tokens,
+                                                      float z_loss, float z2, uint16_t* __restrict__ dlogits,
+                                                      float* __restrict__ row_loss) {
+  constexpr int SEG = NT == 1024 ? 2 : 4, CPS = NT / 4;  // vectors staged at a time; chunks per vector index
+  __shared__ __attribute__((aligned(16))) float st[SEG][CPS][36];
   extern __shared__ float parts[];
-  __shared__ float red[4];
+  __shared__ float red[2][NT / 64];
+  __shared__ float total;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, t = threadIdx.x;
   const int64_t row = blockIdx.x;
   const uint16_t* lr = logits + row * vocab;
-  const int64_t n8 = vocab >> 3;
-  uint4 raw[kXentQ];
+  const int n8 = vocab >> 3, tail = vocab & 7, nv = n8 + (tail ? 1 : 0);
+  Row8 raw[Q];
 #pragma unroll
-  for (int q = 0; q < kXentQ; ++q) {
-    const int64_t j8 = t + 256 * q;
-    raw[q] = (j8 < n8) ? reinterpret_cast<const uint4*>(lr)[j8] : make_uint4(0u, 0u, 0u, 0u);
+  for (int q = 0; q < Q; ++q) {
+    const int j8 = t + NT * q;
+    if (j8 < n8) {
+      raw[q] = *reinterpret_cast<const Row8*>(lr + 8 * (int64_t)j8);
+    } else if (j8 < nv) {  // the partial last vector, filled up with its first logit
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        raw[q].w[i] = (uint32_t)lr[8 * j8 + (2 * i < tail ? 2 * i : 0)] |
+                      ((uint32_t)lr[8 * j8 + (2 * i + 1 < tail ? 2 * i + 1 : 0)] << 16);
+    }
   }
-  float m = -__builtin_inff();
+  float m = -__builtin_inff(), lo = __builtin_inff();
 #pragma unroll
-  for (int q = 0; q < kXentQ; ++q) {
-    if (t + 256 * q < n8) {
+  for (int q = 0; q < Q; ++q) {
+    if (t + NT * q < nv) {
       float f[8];
-      ldb8_regs(raw[q], f);
+      widen_row8(raw[q], f);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) m = fmaxf(m, f[i]);
+      for (int i = 0; i < 8; ++i) {
+        m = fmaxf(m, f[i]);
+        lo = fminf(lo, f[i]);
+      }
     }
   }
   m = wave_max(m);
-  if (lane == 0) red[w] = m;
+  lo = -wave_max(-lo);
+  if (lane == 0) {
+    red[0][w] = m;
+    red[1][w] = lo;
+  }
   __syncthreads();
-  m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  const int64_t nc = (vocab + kChunk - 1) / kChunk;
-  const int nseg = (int)((vocab + 2047) / 2048);
 #pragma unroll
-  for (int s0 = 0; s0 < kXentQ; s0 += 4) {
-    if (s0 < nseg) {
+  for (int i = 0; i < NT / 64; ++i) {
+    m = fmaxf(m, red[0][i]);
+    lo = fminf(lo, red[1][i]);
+  }
+  const bool mid = cexp_is_mid(lo - m);  // no logit of the row is far enough below m for a zero
+  float e[EXPS ? Q : 1][8];
+  auto exps = [&](auto all_mid, const Row8& r, float (&x)[8]) __attribute__((always_inline)) {
+    float f[8];
+    widen_row8(r, f);
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const int sg = s0 + b;
-        if (sg < kXentQ && sg < nseg && t + 256 * sg < n8) {
-          float f[8];
-          ldb8_regs(raw[sg], f);
-          float* dst = &st[b].t[t >> 2][8 * (t & 3)];
+    for (int i = 0; i < 8; ++i) x[i] = all_mid.value ? cexp_mid(f[i] - m) : cexp_neg(f[i] - m);
+  };
+  const int nc = (vocab + kChunk - 1) / kChunk;
+  auto sums = [&](auto all_mid) __attribute__((always_inline)) {
 #pragma unroll
-          for (int i = 0; i < 8; ++i) dst[i] = cexp(f[i] - m);
+    for (int s0 = 0; s0 < Q; s0 += SEG) {
+      if (NT * s0 < nv) {
+#pragma unroll
+        for (int b = 0; b < SEG; ++b) {
+          const int q = s0 + b;
+          if (q < Q && t + NT * q < nv) {
+            float x[8];
+            exps(all_mid, raw[q], x);
+            float4* dst = reinterpret_cast<float4*>(&st[b][t >> 2][8 * (t & 3)]);
+            dst[0] = make_float4(x[0], x[1], x[2], x[3]);
+            dst[1] = make_float4(x[4], x[5], x[6], x[7]);
+            if (EXPS) {
+#pragma unroll
+              for (int i = 0; i < 8; ++i) e[q % (EXPS ? Q : 1)][i] = x[i];
+            }
+          }
         }
-      }
-      __syncthreads();
-      const int sg = s0 + w;
-      if (sg < nseg) {
-        const int64_t c = (int64_t)sg * 64 + lane;
-        if (c < nc) {
-          const int64_t k1 = vocab - c * kChunk < kChunk ? vocab - c * kChunk : kChunk;
+        __syncthreads();
+        const int c = CPS * s0 + t;  // this thread's chunk of the staged vectors
+        if (t < SEG * CPS && c < nc) {
+          const float* src = &st[0][0][0] + 36 * t;
           float sacc = 0.0f;
-          for (int i = 0; i < (int)k1; ++i) sacc = sacc + st[w].t[lane][i];
+          const int k1 = vocab - c * kChunk;
+          if (k1 >= kChunk) {
+#pragma unroll
+            for (int i = 0; i < kChunk; i += 4) {
+              const float4 v = *reinterpret_cast<const float4*>(src + i);
+              sacc = sacc + v.x; sacc = sacc + v.y; sacc = sacc + v.z; sacc = sacc + v.w;
+            }
+          } else {
+            for (int i = 0; i < k1; ++i) sacc = sacc + src[i];
+          }
           parts[c] = sacc;
         }
+        __syncthreads();
       }
-      __syncthreads();
     }
+  };
+  if (mid) sums(std::true_type{});
+  else sums(std::false_type{});
+  // Algorithm 2 over the chunk partials: 256 threads, each an aligned block of G of them
+  const int G = (int)block_chunks(nc, 256), np = (nc + G - 1) / G;
+  if (w < 4) {
+    const int c0 = t * G, c1 = c0 + G < nc ? c0 + G : nc;
+    LocalFoldN<5> f;  // G <= 16
+    for (int c = c0; c < c1; ++c) f.push(parts[c]);
+    const int nl = np - 64 * w;
+    const float r = wave_fold(f.result(), nl < 0 ? 0 : (nl > 64 ? 64 : nl));
+    if (lane == 0) red[0][w] = r;
   }
-  const int64_t G = block_chunks(nc, 256);
-  const int64_t c0 = threadIdx.x * G, c1 = (c0 + G < nc) ? c0 + G : nc;
-  LocalFold f;
-  for (int64_t c = c0; c < c1; ++c) f.push(parts[c]);
-  const float S = block_fold(f.result(), (nc + G - 1) / G);
+  __syncthreads();
+  float S = red[0][0];
+  if (64 < np) S = S + red[0][1];
+  if (128 < np) {
+    float b = red[0][2];
+    if (192 < np) b = b + red[0][3];
+    S = S + b;
+  }
   const int32_t y = targets[row];
   const bool valid = y >= 0 && y < vocab;
   // z-loss (weight z_loss, z2 = RN(2 z_loss)): the row loss gains RN(z_loss * RN(lse^2)) and every
@@ -1086,7 +1067,7 @@ __global__ __launch_bounds__(256) void xent_reg_kernel(int64_t rows, int64_t voc
   const bool zl = z_loss != 0.0f;
   const float zt = z2 * lse;
   const float pscale = 1.0f + zt;
-  if (threadIdx.x == 0) {
+  if (t == 0) {
     float ce = lse - bf16_to_f32(lr[valid ? y : 0]);
     if (zl) {
       const float l2 = lse * lse;
@@ -1096,26 +1077,44 @@ __global__ __launch_bounds__(256) void xent_reg_kernel(int64_t rows, int64_t voc
     row_loss[row] = valid ? ce : __builtin_nanf("");
   }
   const float rcp = 1.0f / S;
-  if (dlogits) {
+  uint16_t* dr = dlogits + row * vocab;
+  auto out = [&](auto all_mid) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < kXentQ; ++q) {
-      const int64_t j8 = t + 256 * q;
-      if (j8 < n8) {
-        float fv[8];
-        uint16_t h[8];
-        ldb8_regs(raw[q], fv);
+    for (int q = 0; q < Q; ++q) {
+      const int j8 = t + NT * q;
+      if (j8 < nv) {
+        float x[8];
+        if (EXPS) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          float e = cexp(fv[i] - m);
-          float pr = e * rcp;
-          if (zl) pr = pr * pscale;
-          float qd = pr - ((j8 * 8 + i) == y ? 1.0f : 0.0f);
-          h[i] = f32_to_bf16(qd * inv_tokens);
+          for (int i = 0; i < 8; ++i) x[i] = e[q % (EXPS ? Q : 1)][i];
+        } else {
+          exps(all_mid, raw[q], x);
         }
-        stb<8>(dlogits + row * vocab + j8 * 8, h);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = x[i] * rcp;
+        if (zl) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) x[i] = x[i] * pscale;
+        }
+        if ((y >> 3) == j8) {  // the target's one; elsewhere p - 0 = p
+#pragma unroll
+          for (int i = 0; i < 8; ++i) x[i] = x[i] - (8 * j8 + i == y ? 1.0f : 0.0f);
+        }
+        Row8 h;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) h.w[i] = pack_bf16(x[2 * i] * inv_tokens, x[2 * i + 1] * inv_tokens);
+        if (j8 < n8) {
+          *reinterpret_cast<Row8*>(dr + 8 * (int64_t)j8) = h;
+        } else {
+#pragma unroll
+          for (int i = 0; i < 7; ++i)
+            if (i < tail) dr[8 * j8 + i] = (uint16_t)(h.w[i >> 1] >> (16 * (i & 1)));
+        }
       }
     }
-  }
+  };
+  if (EXPS || mid) out(std::true_type{});
+  else out(std::false_type{});
 }
 
 // mean_loss = RN(R1(row_loss) * inv_tokens): one workgroup.
@@ -1128,7 +1127,15 @@ __global__ __launch_bounds__(256) void mean_loss_kernel(int64_t rows, const floa
   for (int64_t c = c0; c < c1; ++c) {
     float s = 0.0f;
     const int64_t k1 = (c + 1) * kChunk < rows ? (c + 1) * kChunk : rows;
-    for (int64_t t = c * kChunk; t < k1; ++t) s = s + row_loss[t];
+    if (k1 - c * kChunk == kChunk) {  // all loads in flight before the chain
+      float v[kChunk];
+#pragma unroll
+      for (int i = 0; i < kChunk; ++i) v[i] = row_loss[c * kChunk + i];
+#pragma unroll
+      for (int i = 0; i < kChunk; ++i) s = s + v[i];
+    } else {
+      for (int64_t t = c * kChunk; t < k1; ++t) s = s + row_loss[t];
+    }
     f.push(s);
   }
   const float S = block_fold(f.result(), (nc + G - 1) / G);
@@ -1140,15 +1147,16 @@ hipError_t xent_launch(int64_t rows, int64_t vocab, const uint16_t* logits, cons
   if (rows > 0) {
     const size_t lds = sizeof(float) * (size_t)((vocab + kChunk - 1) / kChunk);
     const float z2 = 2.0f * z_loss;  // exact
-    if (vocab % 8 == 0 && vocab <= kXentRegVocab && al(logits, 16) && al(dlogits, 16))
-      hipLaunchKernelGGL(xent_reg_kernel, dim3((unsigned)rows), dim3(256), lds, s, rows, vocab, logits, targets,
-                         inv_tokens, z_loss, z2, dlogits, row_loss);
-    else if (vocab % 8 == 0 && al(logits, 16) && al(dlogits, 16))
-      hipLaunchKernelGGL(xent_kernel<8>, dim3((unsigned)rows), dim3(256), lds, s, rows, vocab, logits, targets,
-                         inv_tokens, z_loss, z2, dlogits, row_loss);
-    else
-      hipLaunchKernelGGL(xent_kernel<1>, dim3((unsigned)rows), dim3(256), lds, s, rows, vocab, logits, targets,
-                         inv_tokens, z_loss, z2, dlogits, row_loss);
+    const dim3 grid((unsigned)rows);
+    const int v = (int)vocab;  // at most 131072: 16 vectors of 8 for each of 1024 threads
+#define CANON_XENT(NT, Q, EXPS)                                                                                  \
+  hipLaunchKernelGGL((xent_row_kernel<NT, Q, EXPS>), grid, dim3(NT), lds, s, v, logits, targets, inv_tokens, z_loss, z2, \
+                     dlogits, row_loss)
+    if (vocab <= 256 * 8 * 5) CANON_XENT(256, 5, true);
+    else if (vocab <= 256 * 8 * 13) CANON_XENT(256, 13, true);
+    else if (vocab <= 1024 * 8 * 7) CANON_XENT(1024, 7, false);
+    else CANON_XENT(1024, 16, false);
+#undef CANON_XENT
   }
   if (mean_loss)
     hipLaunchKernelGGL(mean_loss_kernel, dim3(1), dim3(256), 0, s, rows, row_loss, inv_tokens, mean_loss);
