@@ -20,7 +20,14 @@ __device__ __forceinline__ float wave_max(float m) {
   return m;
 }
 
-// ---- W-wide loads and stores (W = 1, 4 or 8 consecutive elements; the caller guarantees alignment) ----
+// ---- W-wide loads and stores (W = 1 or 4 consecutive elements at any element alignment: gfx950's global accesses
+// need none) ----
+struct __attribute__((packed, aligned(4))) F4 {
+  float x, y, z, w;
+};
+struct __attribute__((packed, aligned(2))) H4 {
+  uint32_t x, y;
+};
 template <int W>
 __device__ __forceinline__ void ldf(const float* p, float (&f)[W]) {
   if constexpr (W == 1) {
@@ -28,7 +35,7 @@ __device__ __forceinline__ void ldf(const float* p, float (&f)[W]) {
   } else {
 #pragma unroll
     for (int i = 0; i < W; i += 4) {
-      const float4 v = *reinterpret_cast<const float4*>(p + i);
+      const F4 v = *reinterpret_cast<const F4*>(p + i);
       f[i] = v.x; f[i + 1] = v.y; f[i + 2] = v.z; f[i + 3] = v.w;
     }
   }
@@ -38,18 +45,10 @@ template <int W>
 __device__ __forceinline__ void ldb(const uint16_t* p, float (&f)[W]) {
   if constexpr (W == 1) {
     f[0] = bf16_to_f32(p[0]);
-  } else if constexpr (W == 4) {
-    const uint2 u = *reinterpret_cast<const uint2*>(p);
+  } else {
+    const H4 u = *reinterpret_cast<const H4*>(p);
     f[0] = bf16_to_f32((uint16_t)(u.x & 0xFFFFu)); f[1] = bf16_to_f32((uint16_t)(u.x >> 16));
     f[2] = bf16_to_f32((uint16_t)(u.y & 0xFFFFu)); f[3] = bf16_to_f32((uint16_t)(u.y >> 16));
-  } else {
-    const uint4 u = *reinterpret_cast<const uint4*>(p);
-    const uint32_t w4[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      f[2 * i] = bf16_to_f32((uint16_t)(w4[i] & 0xFFFFu));
-      f[2 * i + 1] = bf16_to_f32((uint16_t)(w4[i] >> 16));
-    }
   }
 }
 
@@ -57,13 +56,8 @@ template <int W>
 __device__ __forceinline__ void stb(uint16_t* p, const uint16_t (&h)[W]) {
   if constexpr (W == 1) {
     p[0] = h[0];
-  } else if constexpr (W == 4) {
-    *reinterpret_cast<uint2*>(p) = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16),
-                                              (uint32_t)h[2] | ((uint32_t)h[3] << 16));
   } else {
-    *reinterpret_cast<uint4*>(p) =
-        make_uint4((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16),
-                   (uint32_t)h[4] | ((uint32_t)h[5] << 16), (uint32_t)h[6] | ((uint32_t)h[7] << 16));
+    *reinterpret_cast<H4*>(p) = H4{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
   }
 }
 
@@ -73,7 +67,48 @@ __device__ __forceinline__ void stf(float* p, const float (&f)[W]) {
     p[0] = f[0];
   } else {
 #pragma unroll
-    for (int i = 0; i < W; i += 4) *reinterpret_cast<float4*>(p + i) = make_float4(f[i], f[i + 1], f[i + 2], f[i + 3]);
+    for (int i = 0; i < W; i += 4) *reinterpret_cast<F4*>(p + i) = F4{f[i], f[i + 1], f[i + 2], f[i + 3]};
+  }
+}
+
+// four elements j .. j + 3 of a row of n, those beyond its end as 0 (not read) or not written
+// (TAIL: n is not a multiple of 4)
+template <bool TAIL>
+__device__ __forceinline__ void ldf4(const float* row, int64_t j, int64_t n, float (&f)[4]) {
+  if (!TAIL || j + 4 <= n) {
+    ldf<4>(row + j, f);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f[i] = j + i < n ? row[j + i] : 0.0f;
+  }
+}
+template <bool TAIL>
+__device__ __forceinline__ void ldb4(const uint16_t* row, int64_t j, int64_t n, float (&f)[4]) {
+  if (!TAIL || j + 4 <= n) {
+    ldb<4>(row + j, f);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f[i] = j + i < n ? bf16_to_f32(row[j + i]) : 0.0f;
+  }
+}
+template <bool TAIL>
+__device__ __forceinline__ void stf4(float* row, int64_t j, int64_t n, const float (&f)[4]) {
+  if (!TAIL || j + 4 <= n) {
+    stf<4>(row + j, f);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (j + i < n) row[j + i] = f[i];
+  }
+}
+template <bool TAIL>
+__device__ __forceinline__ void stb4(uint16_t* row, int64_t j, int64_t n, const uint16_t (&h)[4]) {
+  if (!TAIL || j + 4 <= n) {
+    stb<4>(row + j, h);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (j + i < n) row[j + i] = h[i];
   }
 }
 
@@ -154,39 +189,42 @@ constexpr int kMaxRowChunks = 64 * 16;  // rows up to 32768 terms in the wave ke
 // The wave kernels take 4 rows per workgroup, with parts[] as dynamic LDS of 4 x (chunks per row) floats.
 static inline size_t wave_kernel_lds(int64_t cols) { return sizeof(float) * 4 * (size_t)((cols + kChunk - 1) / kChunk); }
 
-// Register-resident rows (cols <= 2048, a multiple of 4, aligned): lane l holds terms 4l + 256q .. +3 of
-// its row for q < 8, read from memory once.  The chunk chains still run one per lane over a padded LDS
-// transpose of the row (the same staging layout as wave_segment_chunks), then fold across the wavefront.
-constexpr int kRegQ = 8;  // float4 vectors per lane: 64 x 4 x 8 = 2048 terms
+// Register-resident rows (cols <= 2048, or the part H of 2048 terms of a longer one): lane l holds terms
+// 4l + 256q .. +3 of its row, read from memory once.  The chunk chains still run one per lane over an LDS transpose
+// (rows of 36 floats: 16-byte stores and reads without bank conflicts; a wavefront's LDS operations complete in order).
+constexpr int kRegQ = 8;  // 64 x 4 x 8 = 2048 terms
 constexpr int64_t kRegCols = 64 * 4 * kRegQ;
+struct RegStage {
+  float t[64][36];
+};
 
-// Chain of every chunk of one staged row (nc <= 64 chunks, n terms) and the fold: returns the row sum.
-__device__ __forceinline__ float reg_row_sum(WaveStage& st, const float (&e)[kRegQ][4], int64_t n) {
+template <int H = 0, int Q>
+__device__ __forceinline__ float reg_row_sum(RegStage& st, const float (&e)[Q][4], int64_t n) {
   const int lane = threadIdx.x & 63;
-  const int nc = (int)((n + kChunk - 1) / kChunk);
 #pragma unroll
   for (int q = 0; q < kRegQ; ++q) {
     const int local = 256 * q + 4 * lane;
-    if (local < n) {
-      float* dst = &st.t[local >> 5][local & 31];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) dst[t] = e[q][t];
-    }
+    const float(&v)[4] = e[H * kRegQ + q];
+    *reinterpret_cast<float4*>(&st.t[local >> 5][local & 31]) = make_float4(v[0], v[1], v[2], v[3]);
   }
-  __builtin_amdgcn_s_waitcnt(0);
   __builtin_amdgcn_wave_barrier();
+  const int nc = (int)((n + kChunk - 1) / kChunk);
   float p = 0.0f;
-  if (lane < nc) {
-    const int k1 = (int)(n - (int64_t)lane * kChunk < kChunk ? n - (int64_t)lane * kChunk : kChunk);
+  const int k1 = (int)n - lane * kChunk;
+  if (k1 >= kChunk) {
+#pragma unroll
+    for (int i = 0; i < kChunk; i += 4) {
+      const float4 v = *reinterpret_cast<const float4*>(&st.t[lane][i]);
+      p = p + v.x; p = p + v.y; p = p + v.z; p = p + v.w;
+    }
+  } else {
     for (int i = 0; i < k1; ++i) p = p + st.t[lane][i];
   }
-  __builtin_amdgcn_s_waitcnt(0);
-  __builtin_amdgcn_wave_barrier();
   return __shfl(wave_fold(p, nc), 0, 64);
 }
 
 // RMSNorm forward: one wavefront per row, 4 rows per workgroup.
-template <int W, bool F32>
+template <bool TAIL, bool F32>
 __global__ __launch_bounds__(256) void rownorm_fwd_kernel(int64_t rows, int64_t cols, const float* __restrict__ x,
                                                           const uint16_t* __restrict__ gain, float eps, float inv_d,
                                                           void* __restrict__ y, float* __restrict__ rstd) {
@@ -197,35 +235,35 @@ __global__ __launch_bounds__(256) void rownorm_fwd_kernel(int64_t rows, int64_t 
   if (row >= rows) return;
   const int64_t nc = (cols + kChunk - 1) / kChunk;
   const float* xr = x + row * cols;
-  float ss = wave_row_rsum<W>(cols, st[w], dyn + w * nc, [&](int64_t j, float (&f)[W]) {
-    ldf<W>(xr + j, f);
+  float ss = wave_row_rsum<4>(cols, st[w], dyn + w * nc, [&](int64_t j, float (&f)[4]) {
+    ldf4<TAIL>(xr, j, cols, f);
 #pragma unroll
-    for (int i = 0; i < W; ++i) f[i] = f[i] * f[i];
+    for (int i = 0; i < 4; ++i) f[i] = f[i] * f[i];
   }, cols);
   float ms = ss * inv_d;
   float var = ms + eps;
   float r = 1.0f / __builtin_sqrtf(var);
   if (lane == 0) rstd[row] = r;
-  for (int64_t k = (int64_t)lane * W; k < cols; k += 64 * W) {
-    float xv[W], gv[W];
-    uint16_t h[W];
-    ldf<W>(xr + k, xv);
-    ldb<W>(gain + k, gv);
-    float o[W];
+  for (int64_t k = (int64_t)lane * 4; k < cols; k += 64 * 4) {
+    float xv[4], gv[4];
+    uint16_t h[4];
+    ldf4<TAIL>(xr, k, cols, xv);
+    ldb4<TAIL>(gain, k, cols, gv);
+    float o[4];
 #pragma unroll
-    for (int i = 0; i < W; ++i) {
+    for (int i = 0; i < 4; ++i) {
       float xn = xv[i] * r;
       o[i] = xn * gv[i];
       h[i] = f32_to_bf16(o[i]);
     }
-    if (F32) stf<W>((float*)y + row * cols + k, o);
-    else stb<W>((uint16_t*)y + row * cols + k, h);
+    if (F32) stf4<TAIL>((float*)y + row * cols, k, cols, o);
+    else stb4<TAIL>((uint16_t*)y + row * cols, k, cols, h);
   }
 }
 
 // RMSNorm backward (dx): one wavefront per row.
 // res (optional): dx = RN(res + the norm's gradient), the residual addition; dxb (optional): bf16 copy of dx.
-template <int W>
+template <bool TAIL>
 __global__ __launch_bounds__(256) void rownorm_bwd_kernel(int64_t rows, int64_t cols, const float* __restrict__ x,
                                                           const uint16_t* __restrict__ gain,
                                                           const float* __restrict__ rstd,
@@ -240,13 +278,13 @@ __global__ __launch_bounds__(256) void rownorm_bwd_kernel(int64_t rows, int64_t 
   const int64_t nc = (cols + kChunk - 1) / kChunk;
   const float* xr = x + row * cols;
   const float* dyr = dy + row * cols;
-  float dot = wave_row_rsum<W>(cols, st[w], dyn + w * nc, [&](int64_t j, float (&f)[W]) {
-    float dv[W], gv[W], xv[W];
-    ldf<W>(dyr + j, dv);
-    ldb<W>(gain + j, gv);
-    ldf<W>(xr + j, xv);
+  float dot = wave_row_rsum<4>(cols, st[w], dyn + w * nc, [&](int64_t j, float (&f)[4]) {
+    float dv[4], gv[4], xv[4];
+    ldf4<TAIL>(dyr, j, cols, dv);
+    ldb4<TAIL>(gain, j, cols, gv);
+    ldf4<TAIL>(xr, j, cols, xv);
 #pragma unroll
-    for (int i = 0; i < W; ++i) {
+    for (int i = 0; i < 4; ++i) {
       float gy = dv[i] * gv[i];
       f[i] = gy * xv[i];
     }
@@ -256,41 +294,41 @@ __global__ __launch_bounds__(256) void rownorm_bwd_kernel(int64_t rows, int64_t 
   float r3 = r2 * r;
   float dd = dot * inv_d;
   float q = r3 * dd;
-  for (int64_t k = (int64_t)lane * W; k < cols; k += 64 * W) {
-    float dv[W], gv[W], xv[W], o[W];
-    ldf<W>(dyr + k, dv);
-    ldb<W>(gain + k, gv);
-    ldf<W>(xr + k, xv);
+  for (int64_t k = (int64_t)lane * 4; k < cols; k += 64 * 4) {
+    float dv[4], gv[4], xv[4], o[4];
+    ldf4<TAIL>(dyr, k, cols, dv);
+    ldb4<TAIL>(gain, k, cols, gv);
+    ldf4<TAIL>(xr, k, cols, xv);
 #pragma unroll
-    for (int i = 0; i < W; ++i) {
+    for (int i = 0; i < 4; ++i) {
       float gy = dv[i] * gv[i];
       float a = r * gy;
       float b = xv[i] * q;
       o[i] = a - b;
     }
     if (res) {
-      float rv[W];
-      ldf<W>(res + row * cols + k, rv);
+      float rv[4];
+      ldf4<TAIL>(res + row * cols, k, cols, rv);
 #pragma unroll
-      for (int i = 0; i < W; ++i) o[i] = rv[i] + o[i];
+      for (int i = 0; i < 4; ++i) o[i] = rv[i] + o[i];
     }
-    stf<W>(dx + row * cols + k, o);
+    stf4<TAIL>(dx + row * cols, k, cols, o);
     if (dxb) {
-      uint16_t h[W];
+      uint16_t h[4];
 #pragma unroll
-      for (int i = 0; i < W; ++i) h[i] = f32_to_bf16(o[i]);
-      stb<W>(dxb + row * cols + k, h);
+      for (int i = 0; i < 4; ++i) h[i] = f32_to_bf16(o[i]);
+      stb4<TAIL>(dxb + row * cols, k, cols, h);
     }
   }
 }
 
 // RMSNorm forward and backward with register-resident rows (same arithmetic as the kernels above).
-template <bool F32>
+template <bool TAIL, bool F32>
 __global__ __launch_bounds__(256) void rownorm_fwd_reg_kernel(int64_t rows, int64_t cols, const float* __restrict__ x,
                                                               const uint16_t* __restrict__ gain, float eps,
                                                               float inv_d, void* __restrict__ y,
                                                               float* __restrict__ rstd) {
-  __shared__ WaveStage st[4];
+  __shared__ __attribute__((aligned(16))) RegStage st[4];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + w;
   if (row >= rows) return;
@@ -300,7 +338,7 @@ __global__ __launch_bounds__(256) void rownorm_fwd_reg_kernel(int64_t rows, int6
   for (int q = 0; q < kRegQ; ++q) {
     const int64_t j = 256 * q + 4 * lane;
     float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (j < cols) ldf<4>(xr + j, v);
+    if (j < cols) ldf4<TAIL>(xr, j, cols, v);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       xv[q][t] = v[t];
@@ -318,26 +356,29 @@ __global__ __launch_bounds__(256) void rownorm_fwd_reg_kernel(int64_t rows, int6
     if (j < cols) {
       float gv[4], o[4];
       uint16_t h[4];
-      ldb<4>(gain + j, gv);
+      ldb4<TAIL>(gain, j, cols, gv);
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         float xn = xv[q][t] * r;
         o[t] = xn * gv[t];
         h[t] = f32_to_bf16(o[t]);
       }
-      if (F32) stf<4>((float*)y + row * cols + j, o);
-      else stb<4>((uint16_t*)y + row * cols + j, h);
+      if (F32) stf4<TAIL>((float*)y + row * cols, j, cols, o);
+      else stb4<TAIL>((uint16_t*)y + row * cols, j, cols, h);
     }
   }
 }
 
-__global__ __launch_bounds__(256) void rownorm_bwd_reg_kernel(int64_t rows, int64_t cols, const float* __restrict__ x,
+// (bounded to 128 registers, four wavefronts per SIMD: 62.8 -> 58.1 us with the gain's part at 8192 x 2048; with TAIL
+// that spills, 69.5 -> 76.5 us at 8192 x 2047)
+template <bool TAIL>
+__global__ __launch_bounds__(256, TAIL ? 3 : 4) void rownorm_bwd_reg_kernel(int64_t rows, int64_t cols, const float* __restrict__ x,
                                                               const uint16_t* __restrict__ gain,
                                                               const float* __restrict__ rstd,
                                                               const float* __restrict__ dy, float inv_d,
                                                               float* __restrict__ dx, const float* __restrict__ res,
                                                               uint16_t* __restrict__ dxb) {
-  __shared__ WaveStage st[4];
+  __shared__ __attribute__((aligned(16))) RegStage st[4];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + w;
   if (row >= rows) return;
@@ -349,9 +390,9 @@ __global__ __launch_bounds__(256) void rownorm_bwd_reg_kernel(int64_t rows, int6
     const int64_t j = 256 * q + 4 * lane;
     float dv[4] = {0.0f, 0.0f, 0.0f, 0.0f}, gv[4] = {0.0f, 0.0f, 0.0f, 0.0f}, xx[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if (j < cols) {
-      ldf<4>(dyr + j, dv);
-      ldb<4>(gain + j, gv);
-      ldf<4>(xr + j, xx);
+      ldf4<TAIL>(dyr, j, cols, dv);
+      ldb4<TAIL>(gain, j, cols, gv);
+      ldf4<TAIL>(xr, j, cols, xx);
     }
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -379,42 +420,63 @@ __global__ __launch_bounds__(256) void rownorm_bwd_reg_kernel(int64_t rows, int6
       }
       if (res) {
         float rv[4];
-        ldf<4>(res + row * cols + j, rv);
+        ldf4<TAIL>(res + row * cols, j, cols, rv);
 #pragma unroll
         for (int t = 0; t < 4; ++t) o[t] = rv[t] + o[t];
       }
-      stf<4>(dx + row * cols + j, o);
+      stf4<TAIL>(dx + row * cols, j, cols, o);
       if (dxb) {
         uint16_t h[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) h[t] = f32_to_bf16(o[t]);
-        stb<4>(dxb + row * cols + j, h);
+        stb4<TAIL>(dxb + row * cols, j, cols, h);
       }
     }
   }
 }
 
 // dgain[k] = R1 over rows t of RN(dy[t,k] * RN(x[t,k] * rstd[t])), in two launches.  First every (chunk of
-// 32 rows, column) chain, one per thread (lane = column, so row reads are coalesced), into part[c][k];
+// 32 rows, column) chain, V per thread (columns along the lanes, so row reads are coalesced), into part[c][k];
 // then per column Algorithm 2 over its chunk partials in ascending order: a workgroup of 16 wavefronts
 // takes 64 columns, wavefront q folds the aligned power-of-two group of chunks [q*G, q*G + G), and the 16
 // group results are folded with the pass-through rule.
-__global__ __launch_bounds__(256) void rownorm_dgain_part_kernel(int64_t rows, int64_t cols,
-                                                                 const float* __restrict__ x,
-                                                                 const float* __restrict__ rstd,
-                                                                 const float* __restrict__ dy,
-                                                                 float* __restrict__ part) {
-  const int64_t col = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// A thread takes V columns and has B rows in flight before their chain steps: V = 4, B = 4 where rows are a multiple of
+// 4 long, V = 1, B = 8 otherwise (with the dx kernel, one row in flight -> this: 62.8 -> 57.9 us at 8192 x 2048,
+// 24.8 -> 20.3 at 2048 x 2048, 91 -> 70 at 8192 x 2047, where V = 4 with a tail takes 80).
+template <int V, int B>
+__global__ __launch_bounds__(256 / V) void rownorm_dgain_part_kernel(int64_t rows, int64_t cols,
+                                                                     const float* __restrict__ x,
+                                                                     const float* __restrict__ rstd,
+                                                                     const float* __restrict__ dy,
+                                                                     float* __restrict__ part) {
+  const int64_t col = (int64_t)blockIdx.x * 256 + threadIdx.x * V;
   const int64_t c = blockIdx.y;
   if (col >= cols) return;
   const int64_t t0 = c * kChunk, t1 = (t0 + kChunk < rows) ? t0 + kChunk : rows;
-  float s = 0.0f;
-  for (int64_t t = t0; t < t1; ++t) {
-    float xh = x[t * cols + col] * rstd[t];
-    float pr = dy[t * cols + col] * xh;
-    s = s + pr;
-  }
-  part[c * cols + col] = s;
+  float s[V] = {};
+  auto steps = [&](int64_t t, auto n) __attribute__((always_inline)) {
+    constexpr int N = decltype(n)::value;
+    float xv[N][V], dv[N][V];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      ldf<V>(x + (t + i) * cols + col, xv[i]);
+      ldf<V>(dy + (t + i) * cols + col, dv[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const float r = rstd[t + i];
+#pragma unroll
+      for (int k = 0; k < V; ++k) {
+        float xh = xv[i][k] * r;
+        float pr = dv[i][k] * xh;
+        s[k] = s[k] + pr;
+      }
+    }
+  };
+  int64_t t = t0;
+  for (; t + B <= t1; t += B) steps(t, std::integral_constant<int, B>{});
+  for (; t < t1; ++t) steps(t, std::integral_constant<int, 1>{});
+  stf<V>(part + c * cols + col, s);
 }
 
 constexpr int kDgainGroups = 16;
@@ -453,7 +515,20 @@ __global__ __launch_bounds__(1024) void rownorm_dgain_fold_kernel(int64_t rows, 
   }
 }
 
-static inline bool al(const void* p, unsigned a) { return ((uintptr_t)p & (a - 1)) == 0; }
+// Rows of up to 2048 terms stay in registers; longer ones are read again for the output (norm forward / backward at
+// 4096 x 4096: 30.5 / 53 us; held in 172 / 296 registers instead, 33 / 58).  TAIL variants take a row length that is
+// no multiple of 4 (the last vector by element; without them every row element by element, 8192 x 2047 forward 55 us
+// instead of 25).
+#define CANON_ROW_KERNEL(LAUNCH, REG, REG_TAIL, GEN, GEN_TAIL)  \
+  do {                                                          \
+    if (cols <= kRegCols) {                                     \
+      if (cols % 4 == 0) LAUNCH(REG, 0);                        \
+      else LAUNCH(REG_TAIL, 0);                                 \
+    } else {                                                    \
+      if (cols % 4 == 0) LAUNCH(GEN, wave_kernel_lds(cols));    \
+      else LAUNCH(GEN_TAIL, wave_kernel_lds(cols));             \
+    }                                                           \
+  } while (0)
 
 template <bool F32>
 static hipError_t rownorm_fwd_any(int64_t rows, int64_t cols, const float* x, const uint16_t* gain, float eps,
@@ -461,16 +536,11 @@ static hipError_t rownorm_fwd_any(int64_t rows, int64_t cols, const float* x, co
   if (rows == 0) return hipSuccess;
   const float inv_d = (float)(1.0 / (double)cols);  // RN32(1/cols), correctly rounded
   const dim3 grid((unsigned)((rows + 3) / 4));
-  const size_t lds = wave_kernel_lds(cols);
-  const unsigned ya = F32 ? 16 : 8;
-  if (cols % 4 == 0 && cols <= kRegCols && al(x, 16) && al(gain, 8) && al(y, ya))
-    hipLaunchKernelGGL(rownorm_fwd_reg_kernel<F32>, grid, dim3(256), 0, s, rows, cols, x, gain, eps, inv_d, y, rstd);
-  else if (cols % 4 == 0 && al(x, 16) && al(gain, 8) && al(y, ya))
-    hipLaunchKernelGGL((rownorm_fwd_kernel<4, F32>), grid, dim3(256), lds, s, rows, cols, x, gain, eps, inv_d, y,
-                       rstd);
-  else
-    hipLaunchKernelGGL((rownorm_fwd_kernel<1, F32>), grid, dim3(256), lds, s, rows, cols, x, gain, eps, inv_d, y,
-                       rstd);
+#define CANON_NORM(K, LDS) \
+  hipLaunchKernelGGL(K, grid, dim3(256), LDS, s, rows, cols, x, gain, eps, inv_d, y, rstd)
+  CANON_ROW_KERNEL(CANON_NORM, (rownorm_fwd_reg_kernel<false, F32>), (rownorm_fwd_reg_kernel<true, F32>),
+                   (rownorm_fwd_kernel<false, F32>), (rownorm_fwd_kernel<true, F32>));
+#undef CANON_NORM
   return hipGetLastError();
 }
 
@@ -497,24 +567,20 @@ hipError_t rownorm_bwd_launch(int64_t rows, int64_t cols, const float* x, const 
   const float inv_d = (float)(1.0 / (double)cols);
   if (dgain) {
     const int64_t nc = (rows + kChunk - 1) / kChunk;
-    hipLaunchKernelGGL(rownorm_dgain_part_kernel, dim3((unsigned)((cols + 255) / 256), (unsigned)nc), dim3(256), 0,
-                       s, rows, cols, x, rstd, dy, dx);
+    const dim3 pgrid((unsigned)((cols + 255) / 256), (unsigned)nc);
+    if (cols % 4 == 0)
+      hipLaunchKernelGGL((rownorm_dgain_part_kernel<4, 4>), pgrid, dim3(64), 0, s, rows, cols, x, rstd, dy, dx);
+    else
+      hipLaunchKernelGGL((rownorm_dgain_part_kernel<1, 8>), pgrid, dim3(256), 0, s, rows, cols, x, rstd, dy, dx);
     hipLaunchKernelGGL(rownorm_dgain_fold_kernel, dim3((unsigned)((cols + 63) / 64)), dim3(1024), 0, s, rows, cols,
                        dx, dgain);
   }
   const dim3 grid((unsigned)((rows + 3) / 4));
-  const size_t lds = wave_kernel_lds(cols);
-  const bool v4 = cols % 4 == 0 && al(x, 16) && al(gain, 8) && al(dy, 16) && al(dx, 16) && (!res || al(res, 16)) &&
-                  (!dxb || al(dxb, 8));
-  if (v4 && cols <= kRegCols)
-    hipLaunchKernelGGL(rownorm_bwd_reg_kernel, grid, dim3(256), 0, s, rows, cols, x, gain, rstd, dy, inv_d, dx, res,
-                       dxb);
-  else if (v4)
-    hipLaunchKernelGGL(rownorm_bwd_kernel<4>, grid, dim3(256), lds, s, rows, cols, x, gain, rstd, dy, inv_d, dx, res,
-                       dxb);
-  else
-    hipLaunchKernelGGL(rownorm_bwd_kernel<1>, grid, dim3(256), lds, s, rows, cols, x, gain, rstd, dy, inv_d, dx, res,
-                       dxb);
+#define CANON_NORM(K, LDS) \
+  hipLaunchKernelGGL(K, grid, dim3(256), LDS, s, rows, cols, x, gain, rstd, dy, inv_d, dx, res, dxb)
+  CANON_ROW_KERNEL(CANON_NORM, rownorm_bwd_reg_kernel<false>, rownorm_bwd_reg_kernel<true>, rownorm_bwd_kernel<false>,
+                   rownorm_bwd_kernel<true>);
+#undef CANON_NORM
   return hipGetLastError();
 }
 
@@ -523,7 +589,7 @@ hipError_t rownorm_bwd_launch(int64_t rows, int64_t cols, const float* x, const 
 // s[r] = RN(RN(2 * RN(R1(|w[r,:]|) * RN(1/cols))) * RN32(1/sqrt(127))).  One wavefront per row.
 constexpr uint32_t kInvSqrtQmaxBits = 0x3DB5BB09u;  // RN32(1/sqrt(127))
 
-template <int W>
+template <bool TAIL>
 __global__ __launch_bounds__(256) void quant_scales_kernel(int64_t rows, int64_t cols, const uint16_t* __restrict__ w,
                                                            float inv_k, float* __restrict__ scale) {
   __shared__ WaveStage st[4];
@@ -533,21 +599,22 @@ __global__ __launch_bounds__(256) void quant_scales_kernel(int64_t rows, int64_t
   if (row >= rows) return;
   const int64_t nc = (cols + kChunk - 1) / kChunk;
   const uint16_t* wr = w + row * cols;
-  const float a = wave_row_rsum<W>(cols, st[wv], dyn + wv * nc, [&](int64_t j, float (&f)[W]) {
-    ldb<W>(wr + j, f);
+  const float a = wave_row_rsum<4>(cols, st[wv], dyn + wv * nc, [&](int64_t j, float (&f)[4]) {
+    ldb4<TAIL>(wr, j, cols, f);
 #pragma unroll
-    for (int i = 0; i < W; ++i) f[i] = __builtin_fabsf(f[i]);
+    for (int i = 0; i < 4; ++i) f[i] = __builtin_fabsf(f[i]);
   }, cols);
   const float mean = a * inv_k;
   const float two = 2.0f * mean;
   if (lane == 0) scale[row] = two * __uint_as_float(kInvSqrtQmaxBits);
 }
 
-// The same for rows held in registers (cols <= 2048, a multiple of 4, 8-byte aligned rows): one read of the row
+// The same for rows held in registers: one read of the row
+template <bool TAIL>
 __global__ __launch_bounds__(256) void quant_scales_reg_kernel(int64_t rows, int64_t cols,
                                                                const uint16_t* __restrict__ w, float inv_k,
                                                                float* __restrict__ scale) {
-  __shared__ WaveStage st[4];
+  __shared__ __attribute__((aligned(16))) RegStage st[4];
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + wv;
   if (row >= rows) return;
@@ -558,7 +625,7 @@ __global__ __launch_bounds__(256) void quant_scales_reg_kernel(int64_t rows, int
     const int64_t j = 256 * q + 4 * lane;
     if (j < cols) {
       float f[4];
-      ldb<4>(wr + j, f);
+      ldb4<TAIL>(wr, j, cols, f);
 #pragma unroll
       for (int t = 0; t < 4; ++t) e[q][t] = __builtin_fabsf(f[t]);
     } else {
@@ -576,13 +643,10 @@ hipError_t quant_scales_launch(int64_t rows, int64_t cols, const uint16_t* w, fl
   if (rows == 0) return hipSuccess;
   const float inv_k = (float)(1.0 / (double)cols);  // RN32(1/cols)
   const dim3 grid((unsigned)((rows + 3) / 4));
-  const size_t lds = wave_kernel_lds(cols);
-  if (cols % 4 == 0 && cols <= kRegCols && al(w, 8))
-    hipLaunchKernelGGL(quant_scales_reg_kernel, grid, dim3(256), 0, s, rows, cols, w, inv_k, scale);
-  else if (cols % 4 == 0 && al(w, 8))
-    hipLaunchKernelGGL(quant_scales_kernel<4>, grid, dim3(256), lds, s, rows, cols, w, inv_k, scale);
-  else
-    hipLaunchKernelGGL(quant_scales_kernel<1>, grid, dim3(256), lds, s, rows, cols, w, inv_k, scale);
+#define CANON_SCALES(K, LDS) hipLaunchKernelGGL(K, grid, dim3(256), LDS, s, rows, cols, w, inv_k, scale)
+  CANON_ROW_KERNEL(CANON_SCALES, quant_scales_reg_kernel<false>, quant_scales_reg_kernel<true>,
+                   quant_scales_kernel<false>, quant_scales_kernel<true>);
+#undef CANON_SCALES
   return hipGetLastError();
 }
 
@@ -597,7 +661,7 @@ __device__ __forceinline__ void band_cols(int band, int64_t i, int64_t window, i
   wlo = (window > 0 && lo > 0) ? lo : 0;
   whi = hi < cols ? hi : cols;
 }
-template <int W>
+template <bool TAIL>
 __global__ __launch_bounds__(256) void softmax_causal_kernel(int64_t rows, int64_t cols, const float* __restrict__ raw,
                                                              float scale, int64_t window,
                                                              uint16_t* __restrict__ probs, int band) {
@@ -613,20 +677,20 @@ __global__ __launch_bounds__(256) void softmax_causal_kernel(int64_t rows, int64
   float m = -__builtin_inff();
   // keys before the window are not read: whole wavefront strides below j0 are skipped, and the loads of
   // vectors wholly below j0 are left out (their terms are +0 either way)
-  for (int64_t j = (j0 / (64 * W)) * (64 * W) + (int64_t)lane * W; j <= i; j += 64 * W) {
-    float v[W];
-    ldf<W>(rr + j, v);
+  for (int64_t j = (j0 / (64 * 4)) * (64 * 4) + (int64_t)lane * 4; j <= i; j += 64 * 4) {
+    float v[4];
+    ldf4<TAIL>(rr, j, cols, v);
 #pragma unroll
-    for (int t = 0; t < W; ++t)
+    for (int t = 0; t < 4; ++t)
       if ((j + t <= i && j + t >= j0)) m = fmaxf(m, v[t] * scale);
   }
   m = wave_max(m);
   // masked keys enter the chain as +0 terms
-  const float S = wave_row_rsum<W>(cols, st[w], dyn + w * nc, [&](int64_t j, float (&f)[W]) {
-    float v[W];
-    if (j + W - 1 >= j0) ldf<W>(rr + j, v);
+  const float S = wave_row_rsum<4>(cols, st[w], dyn + w * nc, [&](int64_t j, float (&f)[4]) {
+    float v[4];
+    if (j + 4 - 1 >= j0) ldf4<TAIL>(rr, j, cols, v);
 #pragma unroll
-    for (int t = 0; t < W; ++t) {
+    for (int t = 0; t < 4; ++t) {
       float e = 0.0f;
       if ((j + t <= i && j + t >= j0)) {
         float sc = v[t] * scale;
@@ -638,13 +702,13 @@ __global__ __launch_bounds__(256) void softmax_causal_kernel(int64_t rows, int64
   const float rcp = 1.0f / S;
   int64_t wlo = 0, whi = cols;  // columns written
   band_cols(band, i, window, cols, wlo, whi);
-  for (int64_t j = (wlo / (64 * W)) * (64 * W) + (int64_t)lane * W; j < whi; j += 64 * W) {
-    uint16_t o[W];
-    if (j <= i && j + W - 1 >= j0) {
-      float v[W];
-      ldf<W>(rr + j, v);
+  for (int64_t j = (wlo / (64 * 4)) * (64 * 4) + (int64_t)lane * 4; j < whi; j += 64 * 4) {
+    uint16_t o[4];
+    if (j <= i && j + 4 - 1 >= j0) {
+      float v[4];
+      ldf4<TAIL>(rr, j, cols, v);
 #pragma unroll
-      for (int t = 0; t < W; ++t) {
+      for (int t = 0; t < 4; ++t) {
         o[t] = 0;
         if ((j + t <= i && j + t >= j0)) {
           float sc = v[t] * scale;
@@ -654,155 +718,91 @@ __global__ __launch_bounds__(256) void softmax_causal_kernel(int64_t rows, int64
       }
     } else {
 #pragma unroll
-      for (int t = 0; t < W; ++t) o[t] = 0;
+      for (int t = 0; t < 4; ++t) o[t] = 0;
     }
-    stb<W>(probs + row * cols + j, o);
+    stb4<TAIL>(probs + row * cols, j, cols, o);
   }
 }
 
+// Rows held in registers, read from memory once (cols <= 256 Q, Q = 8 or 16).  A wavefront's vectors q are each wholly
+// outside the visible keys j0 .. i (+0 terms, no work), wholly inside (no masks) or on an edge.  Bound: the reads of
+// the visible scores and the writes of every probability, 268 MB at 16 heads x 2048: 59 us (masks on every term 84);
+// 4 heads x 4096: 58 us (98).
+template <int Q, bool TAIL>
 __global__ __launch_bounds__(256) void softmax_causal_reg_kernel(int64_t rows, int64_t cols,
                                                                  const float* __restrict__ raw, float scale,
                                                                  int64_t window, uint16_t* __restrict__ probs,
                                                                  int band) {
-  __shared__ WaveStage st[4];
+  __shared__ __attribute__((aligned(16))) RegStage st[4];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + w;
   if (row >= rows) return;
-  const int64_t i = row % cols;
-  const int64_t j0 = (window > 0 && i - window + 1 > 0) ? i - window + 1 : 0;
-  const float* rr = raw + row * cols;
-  float e[kRegQ][4];
-#pragma unroll
-  for (int q = 0; q < kRegQ; ++q) {
-    const int64_t j = 256 * q + 4 * lane;
-    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (j < cols && j <= i && j + 3 >= j0) v = *reinterpret_cast<const float4*>(rr + j);
-    e[q][0] = v.x; e[q][1] = v.y; e[q][2] = v.z; e[q][3] = v.w;
-  }
-  float m = -__builtin_inff();
-#pragma unroll
-  for (int q = 0; q < kRegQ; ++q)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int64_t j = 256 * q + 4 * lane + t;
-      if (j < cols && j <= i && j >= j0) m = fmaxf(m, e[q][t] * scale);
-    }
-  m = wave_max(m);
-  // masked keys enter the chain as +0 terms
-#pragma unroll
-  for (int q = 0; q < kRegQ; ++q)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int64_t j = 256 * q + 4 * lane + t;
-      float x = 0.0f;
-      if (j < cols && j <= i && j >= j0) {
-        float sc = e[q][t] * scale;
-        x = cexp_neg(sc - m);
-      }
-      e[q][t] = x;
-    }
-  const float S = reg_row_sum(st[w], e, cols);
-  const float rcp = 1.0f / S;
-  int64_t wlo = 0, whi = cols;  // columns written
-  band_cols(band, i, window, cols, wlo, whi);
-#pragma unroll
-  for (int q = 0; q < kRegQ; ++q) {
-    const int64_t j = 256 * q + 4 * lane;
-    if (j < whi && j + 3 >= wlo) {
-      uint16_t o[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) o[t] = ((j + t <= i && j + t >= j0)) ? f32_to_bf16(e[q][t] * rcp) : (uint16_t)0;
-      stb<4>(probs + row * cols + j, o);
-    }
-  }
-}
-
-// Rows of 2048 < cols <= 4096 terms held in registers (lane l: terms 4l + 256q .. +3 for q < 16), read from
-// memory once.  The chains run in two halves of 64 chunks through the same padded LDS transpose as
-// wave_segment_chunks (lane c: chunk c, then chunk 64 + c), and the nc partials are folded as in
-// wave_row_rsum (fold_parts).
-constexpr int kReg2Q = 16;
-constexpr int64_t kReg2Cols = 64 * 4 * kReg2Q;
-__global__ __launch_bounds__(256) void softmax_causal_reg2_kernel(int64_t rows, int64_t cols,
-                                                                  const float* __restrict__ raw, float scale,
-                                                                  int64_t window, uint16_t* __restrict__ probs,
-                                                                  int band) {
-  __shared__ WaveStage st[4];
-  extern __shared__ float dyn[];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + w;
-  if (row >= rows) return;
-  const int64_t nc = (cols + kChunk - 1) / kChunk;
-  float* parts = dyn + w * nc;
-  const int i = (int)(row % cols);  // cols <= 4096: column indices fit in int
+  const int i = __builtin_amdgcn_readfirstlane((int)(row % cols));  // column indices fit in int
   const int j0 = (window > 0 && i - window + 1 > 0) ? (int)(i - window + 1) : 0;
-  const int ncol = (int)cols;
   const float* rr = raw + row * cols;
-  float e[kReg2Q][4];
+  auto any = [&](int q) { return 256 * q <= i && 256 * q + 255 >= j0; };   // some visible key in vectors q
+  auto all = [&](int q) { return 256 * q + 255 <= i && 256 * q >= j0; };   // nothing but visible keys
+  float e[Q][4];
 #pragma unroll
-  for (int q = 0; q < kReg2Q; ++q) {
+  for (int q = 0; q < Q; ++q) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) e[q][t] = 0.0f;
     const int j = 256 * q + 4 * lane;
-    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (j < ncol && j <= i && j + 3 >= j0) v = *reinterpret_cast<const float4*>(rr + j);
-    e[q][0] = v.x; e[q][1] = v.y; e[q][2] = v.z; e[q][3] = v.w;
+    if (any(q) && j <= i && j + 3 >= j0) ldf4<TAIL>(rr, j, cols, e[q]);
   }
   float m = -__builtin_inff();
 #pragma unroll
-  for (int q = 0; q < kReg2Q; ++q)
+  for (int q = 0; q < Q; ++q) {
+    if (!any(q)) continue;
+    const int j = 256 * q + 4 * lane;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int j = 256 * q + 4 * lane + t;
-      if (j < ncol && j <= i && j >= j0) m = fmaxf(m, e[q][t] * scale);
+    for (int t = 0; t < 4; ++t) e[q][t] = e[q][t] * scale;
+    if (all(q)) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) m = fmaxf(m, e[q][t]);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (j + t <= i && j + t >= j0) m = fmaxf(m, e[q][t]);
     }
+  }
   m = wave_max(m);
   // masked keys enter the chain as +0 terms
 #pragma unroll
-  for (int q = 0; q < kReg2Q; ++q)
+  for (int q = 0; q < Q; ++q) {
+    if (!any(q)) continue;
+    const int j = 256 * q + 4 * lane;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int j = 256 * q + 4 * lane + t;
-      float x = 0.0f;
-      if (j < ncol && j <= i && j >= j0) {
-        float sc = e[q][t] * scale;
-        x = cexp_neg(sc - m);
-      }
-      e[q][t] = x;
+    for (int t = 0; t < 4; ++t) e[q][t] = cexp_neg(e[q][t] - m);
+    if (!all(q)) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (!(j + t <= i && j + t >= j0)) e[q][t] = 0.0f;
     }
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
-#pragma unroll
-    for (int q = 0; q < kReg2Q / 2; ++q) {
-      const int local = 256 * q + 4 * lane;
-      if (2048 * half + local < ncol) {
-        float* dst = &st[w].t[local >> 5][local & 31];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) dst[t] = e[q + (kReg2Q / 2) * half][t];
-      }
-    }
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
-    const int c = 64 * half + lane;
-    if (c < nc) {
-      const int k1 = ncol - c * (int)kChunk < (int)kChunk ? ncol - c * (int)kChunk : (int)kChunk;
-      float p = 0.0f;
-      for (int k = 0; k < k1; ++k) p = p + st[w].t[lane][k];
-      parts[c] = p;
-    }
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
   }
-  const float S = fold_parts(parts, nc);
+  float S = reg_row_sum<0>(st[w], e, cols < kRegCols ? cols : kRegCols);
+  if constexpr (Q > kRegQ) {  // 64 chunks are a complete subtree: the other half adds last
+    if (i >= kRegCols) S = S + reg_row_sum<1>(st[w], e, cols - kRegCols);
+    else S = S + 0.0f;
+  }
   const float rcp = 1.0f / S;
   int64_t wlo = 0, whi = cols;  // columns written
   band_cols(band, i, window, cols, wlo, whi);
 #pragma unroll
-  for (int q = 0; q < kReg2Q; ++q) {
+  for (int q = 0; q < Q; ++q) {
     const int j = 256 * q + 4 * lane;
     if (j < whi && j + 3 >= wlo) {
-      uint16_t o[4];
+      uint16_t o[4] = {0, 0, 0, 0};
+      if (any(q)) {  // a masked key's probability is +0 * rcp, a NaN if S is: keep its zero
 #pragma unroll
-      for (int t = 0; t < 4; ++t) o[t] = ((j + t <= i && j + t >= j0)) ? f32_to_bf16(e[q][t] * rcp) : (uint16_t)0;
-      stb<4>(probs + row * cols + j, o);
+        for (int t = 0; t < 4; ++t) o[t] = f32_to_bf16(e[q][t] * rcp);
+        if (!all(q)) {
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            if (!(j + t <= i && j + t >= j0)) o[t] = 0;
+        }
+      }
+      stb4<TAIL>(probs + row * cols, j, cols, o);
     }
   }
 }
@@ -815,6 +815,7 @@ constexpr int64_t kBandWin = 512;
 struct BandStage {
   float t[24][33];
 };
+template <bool TAIL>
 __global__ __launch_bounds__(256) void softmax_band_kernel(int64_t rows, int64_t cols, const float* __restrict__ raw,
                                                            float scale, int64_t window, uint16_t* __restrict__ probs,
                                                            int band) {
@@ -834,9 +835,10 @@ __global__ __launch_bounds__(256) void softmax_band_kernel(int64_t rows, int64_t
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     const int64_t j = base + 256 * q + 4 * lane;
-    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (j < cols && j <= i && j + 3 >= j0) v = *reinterpret_cast<const float4*>(rr + j);
-    e[q][0] = v.x; e[q][1] = v.y; e[q][2] = v.z; e[q][3] = v.w;
+    float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (j <= i && j + 3 >= j0) ldf4<TAIL>(rr, j, cols, v);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) e[q][t] = v[t];
   }
   float m = -__builtin_inff();
 #pragma unroll
@@ -891,7 +893,7 @@ __global__ __launch_bounds__(256) void softmax_band_kernel(int64_t rows, int64_t
 #pragma unroll
       for (int t = 0; t < 4; ++t) o[t] = seen(j + t) ? f32_to_bf16(x[t] * rcp) : (uint16_t)0;
     }
-    stb<4>(probs + row * cols + j, o);
+    stb4<TAIL>(probs + row * cols, j, cols, o);
   }
 }
 
@@ -899,21 +901,22 @@ hipError_t softmax_causal_launch(int64_t rows, int64_t cols, const float* raw, f
                                  uint16_t* probs, hipStream_t s, int band) {
   if (rows == 0) return hipSuccess;
   const dim3 grid((unsigned)((rows + 3) / 4));
-  const size_t lds = wave_kernel_lds(cols);
-  if (window > 0 && window <= kBandWin && cols % 4 == 0 && al(raw, 16) && al(probs, 8))
-    hipLaunchKernelGGL(softmax_band_kernel, grid, dim3(256), lds, s, rows, cols, raw, scale, window, probs, band);
-  else if (cols % 4 == 0 && cols <= kRegCols && al(raw, 16) && al(probs, 8))
-    hipLaunchKernelGGL(softmax_causal_reg_kernel, grid, dim3(256), 0, s, rows, cols, raw, scale, window, probs,
-                       band);
-  else if (cols % 4 == 0 && cols <= kReg2Cols && al(raw, 16) && al(probs, 8))
-    hipLaunchKernelGGL(softmax_causal_reg2_kernel, grid, dim3(256), lds, s, rows, cols, raw, scale, window, probs,
-                       band);
-  else if (cols % 4 == 0 && al(raw, 16) && al(probs, 8))
-    hipLaunchKernelGGL(softmax_causal_kernel<4>, grid, dim3(256), lds, s, rows, cols, raw, scale, window, probs,
-                       band);
-  else
-    hipLaunchKernelGGL(softmax_causal_kernel<1>, grid, dim3(256), lds, s, rows, cols, raw, scale, window, probs,
-                       band);
+#define CANON_SOFTMAX(K, LDS) \
+  hipLaunchKernelGGL(K, grid, dim3(256), LDS, s, rows, cols, raw, scale, window, probs, band)
+  if (window > 0 && window <= kBandWin) {
+    if (cols % 4 == 0) CANON_SOFTMAX(softmax_band_kernel<false>, wave_kernel_lds(cols));
+    else CANON_SOFTMAX(softmax_band_kernel<true>, wave_kernel_lds(cols));
+  } else {
+    if (cols > kRegCols && cols <= 2 * kRegCols) {
+      if (cols % 4 == 0) CANON_SOFTMAX((softmax_causal_reg_kernel<2 * kRegQ, false>), 0);
+      else CANON_SOFTMAX((softmax_causal_reg_kernel<2 * kRegQ, true>), 0);
+    } else {
+      CANON_ROW_KERNEL(CANON_SOFTMAX, (softmax_causal_reg_kernel<kRegQ, false>),
+                       (softmax_causal_reg_kernel<kRegQ, true>), softmax_causal_kernel<false>,
+                       softmax_causal_kernel<true>);
+    }
+  }
+#undef CANON_SOFTMAX
   return hipGetLastError();
 }
 
