@@ -984,12 +984,7 @@ canon_status canon_adamw(int64_t n_tensors, const int64_t* sizes, uint16_t* cons
   }
   const float c9[9] = {consts->lr, consts->beta1, consts->one_minus_beta1, consts->beta2, consts->one_minus_beta2,
                        consts->inv_bc1, consts->inv_bc2, consts->eps, consts->decay_factor};
-  for (int64_t t = 0; t < n_tensors; ++t) {
-    hipError_t e = adamw_launch(sizes[t], params[t], m[t], v[t], grads[t], decay_mask[t] != 0, c9, nullptr,
-                                nullptr, as_stream(stream));
-    if (e != hipSuccess) return CANON_EDEVICE;
-  }
-  return CANON_OK;
+  return dev(adamw_launch(n_tensors, sizes, params, m, v, grads, decay_mask, c9, nullptr, nullptr, as_stream(stream)));
 }
 
 size_t canon_clip_grad_norm_workspace_bytes(int64_t n_tensors, const int64_t* sizes) {
@@ -1037,11 +1032,7 @@ canon_status canon_clip_grad_norm(const canon_order* order, int64_t n_tensors, c
   if (n_tensors == 1) {
     src.one = grads[0];
   } else if (n_tensors > 1) {
-    std::vector<const float*> hp(grads, grads + n_tensors);
-    std::vector<int64_t> hs(n_tensors + 1, 0);
-    for (int64_t t = 0; t < n_tensors; ++t) hs[t + 1] = hs[t] + sizes[t];
-    TRY(hipMemcpyAsync(ptr_d, hp.data(), sizeof(float*) * n_tensors, hipMemcpyHostToDevice, s));
-    TRY(hipMemcpyAsync(start_d, hs.data(), sizeof(int64_t) * (n_tensors + 1), hipMemcpyHostToDevice, s));
+    TRY(norm_tables_launch(n_tensors, sizes, grads, ptr_d, start_d, s));
     src.ptr = ptr_d;
     src.start = start_d;
   }
@@ -1054,7 +1045,7 @@ canon_status canon_clip_grad_norm(const canon_order* order, int64_t n_tensors, c
   d.skip_state = clip->skip_state;
   d.skipped_out = clip->skipped_out;
   TRY(gnorm_launch(src, n, vec4 ? 1 : 0, part, d, s));
-  for (int64_t t = 0; t < n_tensors; ++t) TRY(clip_scale_launch(sizes[t], grads[t], coef, s));
+  TRY(clip_scale_launch(n_tensors, sizes, grads, coef, s));
   return CANON_OK;
 }
 
@@ -1344,8 +1335,9 @@ canon_status canon_step(const canon_order* order, const canon_model_cfg* cfg, co
     gscale = L.clip_coef;
     skip = L.skip;
   }
-  for (int64_t t = 0; t < nt; ++t)
-    TRY(adamw_launch(sz[t], params[t], m[t], v[t], g + off[t], decay[t], c9, gscale, skip, s));
+  std::vector<const float*> gt(nt);
+  for (int64_t t = 0; t < nt; ++t) gt[t] = g + off[t];
+  TRY(adamw_launch(nt, sz.data(), params, m, v, gt.data(), decay.data(), c9, gscale, skip, s));
   if (state_digest) {  // the per-step audit hash of the state this step leaves
     std::vector<int64_t> nb;
     step_hash_sizes(cfg, plan, nb);

@@ -84,6 +84,65 @@ hipError_t qlinear_bwd_launch(int64_t T, int64_t N, int64_t K, const void* dy, i
                               hipStream_t s);
 int gemm_max_levels();
 
+// Kernels over a list of tensors take up to kBatchTensors of them per launch, as a table in the kernel arguments
+// (4 KiB at most).  Empty tensors are left out; a tensor owns ceil(size / unit) consecutive workgroups, start[j]
+// being the first of entry j (unused entries 0xFFFFFFFF).
+constexpr int kBatchTensors = 64;
+// the entry of this workgroup: one ballot, a lane per entry
+__device__ __forceinline__ int batch_tensor(const uint32_t (&start)[kBatchTensors]) {
+  return __popcll(__ballot(start[threadIdx.x & 63] <= blockIdx.x)) - 1;
+}
+// The buffers of one launch, sorted; a list may name a buffer twice (it is then updated twice, in order), so a tensor
+// that touches one of these starts the next launch.
+struct BufferSet {
+  uintptr_t lo[4 * kBatchTensors], hi[4 * kBatchTensors];
+  int n = 0;
+  bool add(const void* p, int64_t bytes) {  // false: overlaps a buffer of the set (not added)
+    const uintptr_t a = (uintptr_t)p, b = a + (uintptr_t)bytes;
+    int i = n;
+    while (i > 0 && lo[i - 1] >= a) --i;
+    if ((i > 0 && hi[i - 1] > a) || (i < n && lo[i] < b)) return false;
+    for (int k = n; k > i; --k) {
+      lo[k] = lo[k - 1];
+      hi[k] = hi[k - 1];
+    }
+    lo[i] = a;
+    hi[i] = b;
+    ++n;
+    return true;
+  }
+};
+// add(set, t) enters tensor t's buffers and says whether they were disjoint from those already there
+template <class Add, class Put, class Run>
+hipError_t for_tensor_batches(int64_t nt, const int64_t* sizes, int64_t unit, uint32_t (&start)[kBatchTensors],
+                              Add add, Put put, Run run) {
+  BufferSet used;
+  int j = 0;
+  int64_t blocks = 0;
+  auto flush = [&]() {
+    for (int i = j; i < kBatchTensors; ++i) start[i] = 0xFFFFFFFFu;
+    const hipError_t e = j > 0 ? run((uint32_t)blocks) : hipSuccess;
+    j = 0;
+    blocks = 0;
+    used.n = 0;
+    return e;
+  };
+  for (int64_t t = 0; t < nt; ++t) {
+    if (sizes[t] == 0) continue;
+    const int64_t b = (sizes[t] + unit - 1) / unit;
+    if (j == kBatchTensors || (j > 0 && blocks + b > 0x7FFFFFFF) || !add(used, t)) {
+      const hipError_t e = flush();
+      if (e != hipSuccess) return e;
+      add(used, t);
+    }
+    start[j] = (uint32_t)blocks;
+    put(j, t);
+    blocks += b;
+    ++j;
+  }
+  return flush();
+}
+
 // norm.hip: global gradient norm, clip coefficient, spike decision (R15)
 struct NormSrc {
   const float* one;          // the whole vector in one buffer, or null
@@ -103,8 +162,11 @@ struct ClipDecision {
 };
 int64_t gnorm_blocks(int64_t n);  // block partials the launch needs
 hipError_t gnorm_launch(const NormSrc& src, int64_t n, int vec4, float* part, const ClipDecision& d, hipStream_t s);
-// g <- RN(g * *coef) when *coef < 1
-hipError_t clip_scale_launch(int64_t n, float* g, const float* coef, hipStream_t s);
+// the device tables of src from host arrays, written by a kernel (no copy from pageable memory)
+hipError_t norm_tables_launch(int64_t nt, const int64_t* sizes, float* const* grads, const float** ptr_d,
+                              int64_t* start_d, hipStream_t s);
+// g[t] <- RN(g[t] * *coef) when *coef < 1, for nt tensors
+hipError_t clip_scale_launch(int64_t nt, const int64_t* sizes, float* const* g, const float* coef, hipStream_t s);
 
 // rows.hip
 hipError_t rownorm_fwd_launch(int64_t rows, int64_t cols, const float* x, const uint16_t* gain, float eps,
@@ -180,8 +242,9 @@ hipError_t plan_merge_launch(int64_t n, const float* lower, float* out, hipStrea
 // out = RN(x * inv) (in place allowed)
 hipError_t plan_scale_launch(int64_t n, const float* x, float inv, float* out, hipStream_t s);
 // gscale (may be null): the gradient is taken as RN(g * *gscale) when *gscale < 1 (the R15 clip)
-hipError_t adamw_launch(int64_t n, uint16_t* p, float* m, float* v, const float* g, int decay, const float* consts9,
-                        const float* gscale, const int32_t* skip_flag, hipStream_t s);
+hipError_t adamw_launch(int64_t nt, const int64_t* sizes, uint16_t* const* p, float* const* m, float* const* v,
+                        const float* const* g, const uint8_t* decay, const float* consts9, const float* gscale,
+                        const int32_t* skip_flag, hipStream_t s);
 // R17 int8 P.V per block (attn_i8.hip): qvt int8 [B][Hkv][hd][64 nb] and sv fp32 [B][Hkv][nb] are scratch,
 // nb = attn_pv_blocks(S); hd a multiple of 32 up to 256, S up to 8192.  R18 fixed-point dQ: hd in
 // {16, 32, 64, 128}, F in [1, 62].

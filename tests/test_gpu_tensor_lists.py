@@ -1,0 +1,73 @@
+"""AdamW and the clip over lists of tensors: counts around the 64 tensors of a launch, sizes around the 4096 elements of
+a workgroup and the four-element vectors, empty tensors, buffers off alignment and buffers that are listed twice (each
+listing acts, in order), bit-identical to the oracle."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2609_17380_amd.canon as C
+import paper_2609_17380_amd.inputs as I
+from gpu_util import DEV, assert_bits, host_f32, host_u16
+
+pytestmark = pytest.mark.gpu
+EDGES = [0, 1, 3, 4, 1023, 1025, 4095, 4096, 4097, 4099, 8193]
+
+
+def place(host, dtype, off):
+    t = torch.empty(host.size + off, dtype=dtype, device=DEV)[off:]
+    t.copy_(torch.from_numpy(host.view(np.int16)).view(torch.bfloat16) if dtype == torch.bfloat16
+            else torch.from_numpy(host))
+    return t
+
+
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("count", [1, 63, 64, 65, 130])
+def test_adamw_lists(count, off):
+    print(f"adamw {count} tensors offset {off}", flush=True)
+    sizes = [EDGES[i % len(EDGES)] for i in range(1, count + 1)]
+    p = [I.normal_bf16((n,), i, 40, std=0.1) for i, n in enumerate(sizes)]
+    m = [I.normal_f32((n,), i, 41) for i, n in enumerate(sizes)]
+    v = [np.square(I.normal_f32((n,), i, 42)) for i, n in enumerate(sizes)]
+    g = [I.normal_f32((n,), i, 43) for i, n in enumerate(sizes)]
+    decay = [i % 3 == 0 for i in range(count)]
+    k = I.adamw_constants()
+    dp = [place(x, torch.bfloat16, off) for x in p]
+    dm, dv, dg = ([place(x, torch.float32, off) for x in xs] for xs in (m, v, g))
+    twice = [0, count - 1]  # listed again at the end
+    order = list(range(count)) + twice
+    for part in (list(range(count)), twice):
+        sub = [[xs[i] for i in part] for xs in (p, m, v, g)]
+        oracle.adamw(*sub, [decay[i] for i in part], oracle.AdamWConsts(*k))
+    C.adamw(*([xs[i] for i in order] for xs in (dp, dm, dv, dg)), [decay[i] for i in order], C.AdamWConsts(*k))
+    torch.cuda.synchronize()
+    for i in range(count):
+        assert_bits(host_u16(dp[i]), p[i], f"p{i}")
+        assert_bits(host_f32(dm[i]), m[i], f"m{i}")
+        assert_bits(host_f32(dv[i]), v[i], f"v{i}")
+
+
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("count", [2, 63, 64, 65, 130])
+def test_clip_lists(count, off):
+    print(f"clip {count} tensors offset {off}", flush=True)
+    sizes = [EDGES[i % len(EDGES)] for i in range(1, count + 1)]
+    if off == 0 and count == 65:
+        sizes = [4 * n for n in sizes]  # every boundary on a vector
+    g = [I.normal_f32((n,), i, 43) for i, n in enumerate(sizes)]
+    dg = [place(x, torch.float32, off) for x in g]
+    order = list(range(count)) + [0]  # tensor 0 counts twice and is scaled twice
+    norm_o = oracle.global_norm([g[i] for i in order])
+    coef = np.float32(1.0) / (norm_o + np.float32(1e-6))
+    norm = torch.empty(1, dtype=torch.float32, device=DEV)
+    lst = [dg[i] for i in order]
+    ws = torch.empty(C.clip_grad_norm_workspace_bytes(lst), dtype=torch.uint8, device=DEV)
+    C.clip_grad_norm(lst, C.make_clip(1.0, float("inf"), 0, norm), ws)
+    torch.cuda.synchronize()
+    assert_bits(host_f32(norm), np.array([norm_o], np.float32), "norm")
+    for i in range(count):
+        want = g[i] * coef if coef < 1 else g[i]
+        if i == 0 and coef < 1:
+            want = want * coef
+        assert_bits(host_f32(dg[i]), want, f"g{i}")
