@@ -215,18 +215,13 @@ __global__ __launch_bounds__(256) void attn_pv_i8_kernel(PvArgs a) {
     const float spd = step_daz(sp);
     const bool recip = recip_step_ok(spd);
     const float rsp = recip ? 1.0f / spd : 0.0f;
-    uint32_t word0 = 0, word1 = 0, word2 = 0, word3 = 0;
+    float pf[16];
+    uint32_t word[4];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const float pf = bf16_to_f32((uint16_t)(pwv[e >> 1] >> (16 * (e & 1))));
-      const int8_t c = recip ? quant_recip(pf, spd, rsp) : quant1(pf, spd);
-      const uint32_t bits = (uint32_t)(uint8_t)c << (8 * (e & 3));
-      if (e < 4) word0 |= bits;
-      else if (e < 8) word1 |= bits;
-      else if (e < 12) word2 |= bits;
-      else word3 |= bits;
-    }
-    *reinterpret_cast<uint4*>(As[buf] + pr * LD + pc) = make_uint4(word0, word1, word2, word3);
+    for (int e = 0; e < 16; ++e)  // (a subnormal is flushed by the quantiser's first operation)
+      pf[e] = __uint_as_float((e & 1) ? pwv[e >> 1] & 0xFFFF0000u : pwv[e >> 1] << 16);
+    quant_pack<16>(pf, spd, rsp, recip, word);
+    *reinterpret_cast<uint4*>(As[buf] + pr * LD + pc) = make_uint4(word[0], word[1], word[2], word[3]);
 #pragma unroll
     for (int q = 0; q < NVQ; ++q) {
       const int64_t v = threadIdx.x + 256 * q;

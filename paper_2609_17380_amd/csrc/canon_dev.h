@@ -160,10 +160,10 @@ __device__ __forceinline__ int8_t quant1(float v, float sv) {
 
 // The same quantiser through the reciprocal of a step shared by many values: for a step s in (0, 2^126]
 // (positive, normal, with a normal reciprocal) and rs = RN(1/s), t = RN(v * rs) lies within |v/s| 2^-23
-// (1 + 2^-25) of v/s.  |t| >= 129 means |v/s| > 128.9: the clamp decides.  Otherwise |t - v/s| < 1.6e-5 and
-// |RN(v/s) - v/s| <= 2^-17, so when t is farther than 2^-15 from every half-integer no rounding boundary
-// separates t from RN(v/s) and both round to the same integer; closer than that, the correctly rounded
-// quotient decides.  A NaN t falls through to it as well.
+// (1 + 2^-25) of v/s.  |t| >= 129 means |v/s| > 128.9: the clamp decides, whatever rne(t) is.  Otherwise
+// |t - v/s| < 1.6e-5 and |RN(v/s) - v/s| <= 2^-17, so when t is farther than 2^-15 from every half-integer no
+// rounding boundary separates t from RN(v/s) and both round to the same integer; closer than that (or for an
+// infinite or NaN t), the correctly rounded quotient decides.
 __device__ __forceinline__ bool recip_step_ok(float s) { return s > 0.0f && s <= 0x1p126f; }
 
 __device__ __forceinline__ int8_t quant_recip(float v, float s, float rs) {
@@ -173,6 +173,32 @@ __device__ __forceinline__ int8_t quant_recip(float v, float s, float rs) {
   const float d = fabsf(t - n);  // exact (Sterbenz), at most 1/2
   if (0.5f - d > 0x1p-15f) return (int8_t)(int)fminf(fmaxf(n, -128.0f), 127.0f);
   return quant1(v, s);
+}
+
+// N codes, four to a word: all through the reciprocal without branches (n + 128 converted to a byte with
+// saturation, the conversion also being the clamp, then the offset taken off), and the exact quotients for the
+// whole group in the rare lanes where some value needs one.  Six instructions per value instead of three branches:
+// the row rotation's codes of 8192 x 11264 gradients 90 -> 87 us (461 MB moved), the column rotation's 124 -> 110,
+// int8 P.V of 16 heads x 4096 with a window of 512 88 -> 71.
+template <int N>
+__device__ __forceinline__ void quant_pack(const float (&v)[N], float s, float rs, bool recip, uint32_t (&w)[N / 4]) {
+  bool exact = !recip;
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const float t = v[j] * rs;
+    const float n = __builtin_rintf(t);
+    exact |= !(fabsf(t - n) < 0.5f - 0x1p-15f);
+    w[j >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(n + 128.0f, j & 3, (j & 3) ? w[j >> 2] : 0u);
+  }
+#pragma unroll
+  for (int j = 0; j < N / 4; ++j) w[j] ^= 0x80808080u;
+  if (exact) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const uint32_t b = (uint8_t)quant1(v[j], s);
+      w[j >> 2] = (j & 3) ? w[j >> 2] | (b << (8 * (j & 3))) : b;
+    }
+  }
 }
 
 __device__ __forceinline__ float step_daz(float s) {

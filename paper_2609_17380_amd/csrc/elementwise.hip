@@ -784,14 +784,16 @@ __global__ void quantize_tensor4_kernel(int64_t n, const float* __restrict__ x, 
   const float sv = step_daz(scale[0]);
   const bool recip = recip_step_ok(sv);
   const float rs = recip ? 1.0f / sv : 0.0f;
-  auto qz = [&](float v) -> uint32_t { return (uint8_t)(recip ? quant_recip(v, sv, rs) : quant1(v, sv)); };
   const int64_t n4 = n >> 2;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256) {
-    const float4 v = reinterpret_cast<const float4*>(x)[i];
-    reinterpret_cast<uint32_t*>(q)[i] = qz(v.x) | (qz(v.y) << 8) | (qz(v.z) << 16) | (qz(v.w) << 24);
+    const float4 x4 = reinterpret_cast<const float4*>(x)[i];
+    const float v[4] = {x4.x, x4.y, x4.z, x4.w};
+    uint32_t o[1];
+    quant_pack<4>(v, sv, rs, recip, o);
+    reinterpret_cast<uint32_t*>(q)[i] = o[0];
   }
   const int64_t t = n4 * 4 + (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t < n) q[t] = (int8_t)qz(x[t]);
+  if (t < n) q[t] = recip ? quant_recip(x[t], sv, rs) : quant1(x[t], sv);
 }
 
 // one step for the whole tensor, bf16 input, 16-byte aligned x and 8-byte aligned q: 8 values per thread
@@ -800,20 +802,19 @@ __global__ void quantize_tensor_bf16x8_kernel(int64_t n, const uint16_t* __restr
   const float sv = step_daz(scale[0]);
   const bool recip = recip_step_ok(sv);
   const float rs = recip ? 1.0f / sv : 0.0f;
-  auto qz = [&](float v) -> uint32_t { return (uint8_t)(recip ? quant_recip(v, sv, rs) : quant1(v, sv)); };
   const int64_t n8 = n >> 3;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += (int64_t)gridDim.x * 256) {
     const uint4 h = reinterpret_cast<const uint4*>(x)[i];
     const uint32_t w[4] = {h.x, h.y, h.z, h.w};
     uint32_t o[2];
+    float v[8];
 #pragma unroll
-    for (int k = 0; k < 2; ++k)
-      o[k] = qz(__uint_as_float(w[2 * k] << 16)) | (qz(__uint_as_float(w[2 * k] & 0xFFFF0000u)) << 8) |
-             (qz(__uint_as_float(w[2 * k + 1] << 16)) << 16) | (qz(__uint_as_float(w[2 * k + 1] & 0xFFFF0000u)) << 24);
+    for (int k = 0; k < 8; ++k) v[k] = __uint_as_float((k & 1) ? w[k >> 1] & 0xFFFF0000u : w[k >> 1] << 16);
+    quant_pack<8>(v, sv, rs, recip, o);
     reinterpret_cast<uint2*>(q)[i] = make_uint2(o[0], o[1]);
   }
   const int64_t t = n8 * 8 + (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t < n) q[t] = (int8_t)qz(bf16_to_f32(x[t]));
+  if (t < n) q[t] = recip ? quant_recip(bf16_to_f32(x[t]), sv, rs) : quant1(bf16_to_f32(x[t]), sv);
 }
 
 // one step per row, bf16 input with 16-byte aligned rows (cols a multiple of 8) and 8-byte aligned q: a
@@ -825,18 +826,18 @@ __global__ __launch_bounds__(256) void quantize_rows_bf16x8_kernel(int64_t rows,
   const int64_t g8 = cols >> 3;
   for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
     const float sv = step_daz(scale[r]);
+    const bool recip = recip_step_ok(sv);
+    const float rs = recip ? 1.0f / sv : 0.0f;
     const uint4* xr = reinterpret_cast<const uint4*>(x + r * cols);
     uint2* qr = reinterpret_cast<uint2*>(q + r * cols);
     for (int64_t i = threadIdx.x; i < g8; i += 256) {
       const uint4 h = xr[i];
       const uint32_t w[4] = {h.x, h.y, h.z, h.w};
       uint32_t o[2];
+      float v[8];
 #pragma unroll
-      for (int k = 0; k < 2; ++k)
-        o[k] = (uint32_t)(uint8_t)quant1(__uint_as_float(w[2 * k] << 16), sv) |
-               ((uint32_t)(uint8_t)quant1(__uint_as_float(w[2 * k] & 0xFFFF0000u), sv) << 8) |
-               ((uint32_t)(uint8_t)quant1(__uint_as_float(w[2 * k + 1] << 16), sv) << 16) |
-               ((uint32_t)(uint8_t)quant1(__uint_as_float(w[2 * k + 1] & 0xFFFF0000u), sv) << 24);
+      for (int k = 0; k < 8; ++k) v[k] = __uint_as_float((k & 1) ? w[k >> 1] & 0xFFFF0000u : w[k >> 1] << 16);
+      quant_pack<8>(v, sv, rs, recip, o);
       qr[i] = make_uint2(o[0], o[1]);
     }
   }

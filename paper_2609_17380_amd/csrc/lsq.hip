@@ -5,7 +5,7 @@
 // scale for K features, computed by the caller), where for each element with v = RN(x / s): delta = -128 below
 // the integer range, 127 above it, RN(rne(v) - v) inside; 0 when the step is not > 0 once flushed or v is NaN.
 // Pass 1: one workgroup per aligned block of 1024 chunks (a complete subtree of the padded tree); each
-// wavefront forms 64 chunks of terms at a time from coalesced loads, stages them transposed in LDS so that
+// wavefront forms 64 chunks of terms at a time from coalesced loads (any alignment), stages them transposed in LDS so that
 // lane c runs chunk c's chain, and folds the lanes with the pass-through rule.  Pass 2: one workgroup folds
 // the block sums (each thread a complete subtree of consecutive sums, then across threads) and scales.
 #include <hip/hip_runtime.h>
@@ -19,13 +19,20 @@ namespace canon {
 
 namespace {
 
-constexpr int kSegs = 4;                        // segments of 64 chunks per wavefront
-constexpr int kWaveChunks = 64 * kSegs;         // 256 chunks per wavefront
-constexpr int kBlockChunks = 4 * kWaveChunks;   // 1024 chunks (32768 terms) per workgroup
+constexpr int kWaves = 8;                       // wavefronts of a workgroup
+constexpr int kSegs = 2;                        // segments of 64 chunks per wavefront
+constexpr int kWaveChunks = 64 * kSegs;         // 128 chunks per wavefront
+constexpr int kBlockChunks = kWaves * kWaveChunks;  // 1024 chunks (32768 terms) per workgroup
 constexpr int kSegTerms = 64 * kChunk;          // 2048 terms per segment
 
 struct Stage {
-  float t[64][33];
+  float t[64][36];  // 16-byte stores and reads without bank conflicts
+};
+struct __attribute__((packed, aligned(4))) Dx4 {
+  float f[4];
+};
+struct __attribute__((packed, aligned(2))) X4 {
+  uint32_t w[2];
 };
 
 __device__ __forceinline__ float lsq_delta(float x, float s, bool valid) {
@@ -37,76 +44,92 @@ __device__ __forceinline__ float lsq_delta(float x, float s, bool valid) {
   return __builtin_rintf(v) - v;  // exact: |rne(v) - v| <= 1/2 (Sterbenz)
 }
 
-// terms j .. j+3 (VEC: one 16-byte load of dx and 8 bytes of x; the caller guarantees alignment and that the
-// group lies inside [0, n))
-template <bool VEC>
-__device__ __forceinline__ void terms4(const uint16_t* __restrict__ x, const float* __restrict__ dx, int64_t n,
-                                       int64_t j, float s, bool valid, float (&t)[4]) {
-  if (VEC && j + 4 <= n) {
-    const float4 g = *reinterpret_cast<const float4*>(dx + j);
-    const uint2 h = *reinterpret_cast<const uint2*>(x + j);
-    t[0] = g.x * lsq_delta(bf16_to_f32((uint16_t)(h.x & 0xFFFFu)), s, valid);
-    t[1] = g.y * lsq_delta(bf16_to_f32((uint16_t)(h.x >> 16)), s, valid);
-    t[2] = g.z * lsq_delta(bf16_to_f32((uint16_t)(h.y & 0xFFFFu)), s, valid);
-    t[3] = g.w * lsq_delta(bf16_to_f32((uint16_t)(h.y >> 16)), s, valid);
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      t[i] = (j + i < n) ? dx[j + i] * lsq_delta(bf16_to_f32(x[j + i]), s, valid) : 0.0f;
-  }
-}
-
-template <bool VEC>
-__global__ __launch_bounds__(256) void lsq_block_kernel(int64_t n, const uint16_t* __restrict__ x,
-                                                        const float* __restrict__ dx, const float* __restrict__ sp,
-                                                        float* __restrict__ part) {
+// Workgroup: 1024 chunks over 8 wavefronts, two segments each, the second one's 24 bytes per term group requested
+// before the first one's divisions.  Bound: vector instructions (the correctly rounded quotient) beside 6 bytes per
+// term: 8192 x 2048 terms 30 us (4 wavefronts of four segments, loads one group at a time: 49).
+__global__ __launch_bounds__(64 * kWaves) void lsq_block_kernel(int64_t n, const uint16_t* __restrict__ x,
+                                                                const float* __restrict__ dx,
+                                                                const float* __restrict__ sp,
+                                                                float* __restrict__ part) {
   constexpr int Q = kSegTerms / (64 * 4);  // 4-term groups per lane per segment
-  __shared__ Stage st[4];
-  __shared__ float wsum[4];
+  __shared__ __attribute__((aligned(16))) Stage st[kWaves];
+  __shared__ float wsum[kWaves];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const float s = step_daz(*sp);
   const bool valid = s > 0.0f;
   const int64_t nc = (n + kChunk - 1) / kChunk;
   const int64_t cw = (int64_t)blockIdx.x * kBlockChunks + (int64_t)w * kWaveChunks;  // wave's first chunk
-  LocalFoldN<8> wf;
+  Dx4 g[kSegs][Q];
+  X4 h[kSegs][Q];
+  auto load = [&](int sg) __attribute__((always_inline)) {
+    const int64_t j0 = (cw + 64 * sg) * kChunk;
+    if (j0 + kSegTerms <= n) {
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        g[sg][q] = *reinterpret_cast<const Dx4*>(dx + j0 + 256 * q + 4 * lane);
+        h[sg][q] = *reinterpret_cast<const X4*>(x + j0 + 256 * q + 4 * lane);
+      }
+    } else {  // the last segment, element by element, +0 beyond the end
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        h[sg][q].w[0] = h[sg][q].w[1] = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int64_t j = j0 + 256 * q + 4 * lane + i;
+          g[sg][q].f[i] = j < n ? dx[j] : 0.0f;
+          if (j < n) h[sg][q].w[i >> 1] |= (uint32_t)x[j] << (16 * (i & 1));
+        }
+      }
+    }
+  };
+  load(0);
+  float tot = 0.0f;
+#pragma unroll
   for (int sg = 0; sg < kSegs; ++sg) {
     const int64_t c0 = cw + 64 * sg;
     if (c0 >= nc) break;
+    if (sg + 1 < kSegs && c0 + 64 < nc) load(sg + 1);
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       const int local = 256 * q + 4 * lane;
       float t[4];
-      terms4<VEC>(x, dx, n, c0 * kChunk + local, s, valid, t);
-      float* dst = &st[w].t[local >> 5][local & 31];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) dst[i] = t[i];
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t b = h[sg][q].w[i >> 1];
+        t[i] = g[sg][q].f[i] * lsq_delta(__uint_as_float((i & 1) ? b & 0xFFFF0000u : b << 16), s, valid);
+      }
+      *reinterpret_cast<float4*>(&st[w].t[local >> 5][local & 31]) = make_float4(t[0], t[1], t[2], t[3]);
     }
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_wave_barrier();  // a wavefront's LDS operations complete in order
     float p = 0.0f;
-    const int64_t c = c0 + lane;
-    if (c < nc) {
-      const int k1 = (int)(n - c * kChunk < kChunk ? n - c * kChunk : kChunk);
-      for (int i = 0; i < k1; ++i) p = p + st[w].t[lane][i];
+    const int64_t k1 = n - (c0 + lane) * kChunk;
+    if (k1 >= kChunk) {
+#pragma unroll
+      for (int i = 0; i < kChunk; i += 4) {
+        const float4 v = *reinterpret_cast<const float4*>(&st[w].t[lane][i]);
+        p = p + v.x; p = p + v.y; p = p + v.z; p = p + v.w;
+      }
+    } else {
+      for (int i = 0; i < (int)k1; ++i) p = p + st[w].t[lane][i];
     }
     const int64_t real = nc - c0;
     const float seg = wave_fold(p, real > 64 ? 64 : (int)real);
-    if (lane == 0) wf.push(seg);
-    __builtin_amdgcn_s_waitcnt(0);
+    tot = sg == 0 ? seg : tot + seg;
     __builtin_amdgcn_wave_barrier();
   }
-  if (lane == 0) wsum[w] = wf.result();
+  if (lane == 0) wsum[w] = tot;
   __syncthreads();
-  if (threadIdx.x == 0) {  // the four waves: pairs of complete subtrees, a right one without real chunks passed over
+  if (threadIdx.x == 0) {  // the waves' complete subtrees, a right one without real chunks passed over
     const int64_t cb = (int64_t)blockIdx.x * kBlockChunks;
-    float a = wsum[0];
-    if (cb + kWaveChunks < nc) a = a + wsum[1];
-    if (cb + 2 * kWaveChunks < nc) {
-      float b = wsum[2];
-      if (cb + 3 * kWaveChunks < nc) b = b + wsum[3];
-      a = a + b;
-    }
-    part[blockIdx.x] = a;
+    float v[kWaves];
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) v[q] = wsum[q];
+#pragma unroll
+    for (int d = 1; d < kWaves; d <<= 1)
+#pragma unroll
+      for (int q = 0; q + d < kWaves; q += 2 * d)
+        if (cb + (q + d) * kWaveChunks < nc) v[q] = v[q] + v[q + d];
+    part[blockIdx.x] = v[0];
   }
 }
 
@@ -163,9 +186,7 @@ hipError_t lsq_grad_launch(int64_t n, const uint16_t* x, const float* s, const f
     hipLaunchKernelGGL(lsq_final_kernel, dim3(1), dim3(256), 0, st, (int64_t)0, part, gamma, out);
     return hipGetLastError();
   }
-  const bool vec = n % 4 == 0 && ((uintptr_t)x & 7) == 0 && ((uintptr_t)dx & 15) == 0;
-  if (vec) hipLaunchKernelGGL(lsq_block_kernel<true>, dim3((unsigned)nparts), dim3(256), 0, st, n, x, dx, s, part);
-  else hipLaunchKernelGGL(lsq_block_kernel<false>, dim3((unsigned)nparts), dim3(256), 0, st, n, x, dx, s, part);
+  hipLaunchKernelGGL(lsq_block_kernel, dim3((unsigned)nparts), dim3(64 * kWaves), 0, st, n, x, dx, s, part);
   hipLaunchKernelGGL(lsq_final_kernel, dim3(1), dim3(256), 0, st, nparts, part, gamma, out);
   return hipGetLastError();
 }

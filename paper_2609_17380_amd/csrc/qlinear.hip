@@ -77,7 +77,6 @@ __global__ __launch_bounds__(256) void fwht_kernel(int64_t n, const void* src, i
     recip = recip_step_ok(sv);
     rs = recip ? 1.0f / sv : 0.0f;
   }
-  auto qz = [&](float v) -> uint32_t { return (uint8_t)(recip ? quant_recip(v, sv, rs) : quant1(v, sv)); };
   const int64_t nblk = n / 256;
   for (int64_t blk = ((int64_t)blockIdx.x * 4 + wv) * 4 + (lane >> 4); blk < nblk; blk += (int64_t)gridDim.x * 16) {
     float v[16];
@@ -109,18 +108,19 @@ __global__ __launch_bounds__(256) void fwht_kernel(int64_t n, const void* src, i
     stage_lanes<2>(v, lane);
     stage_lanes<4>(v, lane);
     stage_lanes<8>(v, lane);
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       v[j] = v[j] * 0.0625f;
-      if (MODE == FWHT_QUANT) {
-        w[j >> 2] |= qz(v[j]) << (8 * (j & 3));
-      } else {
+      if (MODE == FWHT_AMAX) {
         const uint32_t u = __float_as_uint(v[j]) & 0x7FFFFFFFu;
         m = u > m ? u : m;
       }
     }
-    if (MODE == FWHT_QUANT) reinterpret_cast<uint4*>(q + blk * 256)[L] = make_uint4(w[0], w[1], w[2], w[3]);
+    if (MODE == FWHT_QUANT) {
+      uint32_t w[4];
+      quant_pack<16>(v, sv, rs, recip, w);
+      reinterpret_cast<uint4*>(q + blk * 256)[L] = make_uint4(w[0], w[1], w[2], w[3]);
+    }
   }
   if (MODE == FWHT_QUANT) return;
 #pragma unroll
@@ -227,17 +227,15 @@ __global__ __launch_bounds__(256) void fwht_cols_kernel(int64_t R, int64_t C, co
     stage_regs<2>(v);
     stage_regs<4>(v);
     stage_regs<8>(v);
-    codes[p][0] = codes[p][1] = codes[p][2] = codes[p][3] = 0u;
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       v[j] = v[j] * 0.0625f;
-      if (MODE == FWHT_QUANT) {
-        codes[p][j >> 2] |= (uint32_t)(uint8_t)(recip ? quant_recip(v[j], sv, rs) : quant1(v[j], sv)) << (8 * (j & 3));
-      } else {
+      if (MODE == FWHT_AMAX) {
         const uint32_t u = __float_as_uint(v[j]) & 0x7FFFFFFFu;
         m = u > m ? u : m;
       }
     }
+    if (MODE == FWHT_QUANT) quant_pack<16>(v, sv, rs, recip, codes[p]);
   }
   if (MODE == FWHT_QUANT) {
     // codes through LDS (the value tile is no longer read once every wavefront passed the barrier):
