@@ -279,10 +279,11 @@ struct AdamWK {
 };
 
 // One launch updates up to kBatchTensors tensors: their table travels in the kernel arguments, a workgroup takes
-// kAdamWBlock consecutive elements of one tensor, four per thread at a time (16-byte accesses, which need no
-// alignment).  Bound: HBM, 24 bytes per parameter.  110 M parameters in 51 tensors: 661 us as one launch per tensor
-// (one element per thread; each launch ramps up and drains on its own), 497 us in one.
-constexpr int kAdamWBlock = 4096;
+// kAdamWBlock consecutive elements of one tensor, two per thread, 256 apart and loaded together.  Bound: HBM, 24 bytes
+// per parameter.  110 M parameters in 51 tensors: 622 us as one launch per tensor (one element per thread; each launch
+// ramps up and drains on its own), 453 us in one; one tensor of 1.2e9: 5203 -> 4899 us.  With 1 or 4 elements per
+// thread 507 / 480 and 5616 / 5226 us, with four 16-byte vectors per thread 489 and 5424.
+constexpr int kAdamWBlock = 512;
 struct AdamWTable {
   uint16_t* p[kBatchTensors];
   float* m[kBatchTensors];
@@ -292,13 +293,6 @@ struct AdamWTable {
   uint64_t decay;                  // bit t: tensor t decays
   uint32_t start[kBatchTensors];   // first workgroup of each tensor; unused entries 0xFFFFFFFF
 };
-struct __attribute__((packed, aligned(4))) AdamF4 {
-  float f[4];
-};
-struct __attribute__((packed, aligned(2))) AdamH4 {
-  uint16_t h[4];
-};
-
 __global__ __launch_bounds__(256) void adamw_kernel(AdamWTable tab, AdamWK k, const float* __restrict__ gscale,
                                                     const int32_t* __restrict__ skip) {
   if (skip && *skip) return;
@@ -331,27 +325,33 @@ __global__ __launch_bounds__(256) void adamw_kernel(AdamWTable tab, AdamWK k, co
     vo = vi;
     ph = f32_to_bf16(p);
   };
+  constexpr int E = kAdamWBlock / 256;  // loads in flight before the arithmetic
+  const int64_t i0t = i0 + threadIdx.x;
+  if (i0 + kAdamWBlock <= n) {
+    uint16_t ph[E];
+    float mo[E], vo[E], gi[E];
 #pragma unroll
-  for (int it = 0; it < kAdamWBlock / 1024; ++it) {
-    const int64_t i = i0 + 1024 * it + 4 * threadIdx.x;
-    if (i + 4 <= n) {
-      AdamH4 ph = *reinterpret_cast<const AdamH4*>(p16 + i);
-      AdamF4 mo = *reinterpret_cast<const AdamF4*>(m + i), vo = *reinterpret_cast<const AdamF4*>(v + i);
-      const AdamF4 gi = *reinterpret_cast<const AdamF4*>(g + i);
+    for (int e = 0; e < E; ++e) {
+      ph[e] = p16[i0t + 256 * e];
+      mo[e] = m[i0t + 256 * e];
+      vo[e] = v[i0t + 256 * e];
+      gi[e] = g[i0t + 256 * e];
+    }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) one(ph.h[e], mo.f[e], vo.f[e], gi.f[e]);
-      *reinterpret_cast<AdamF4*>(m + i) = mo;
-      *reinterpret_cast<AdamF4*>(v + i) = vo;
-      *reinterpret_cast<AdamH4*>(p16 + i) = ph;
-    } else {
-      for (int64_t j = i; j < n; ++j) {
-        uint16_t ph = p16[j];
-        float mo = m[j], vo = v[j];
-        one(ph, mo, vo, g[j]);
-        m[j] = mo;
-        v[j] = vo;
-        p16[j] = ph;
-      }
+    for (int e = 0; e < E; ++e) {
+      one(ph[e], mo[e], vo[e], gi[e]);
+      m[i0t + 256 * e] = mo[e];
+      v[i0t + 256 * e] = vo[e];
+      p16[i0t + 256 * e] = ph[e];
+    }
+  } else {
+    for (int64_t j = i0t; j < n; j += 256) {
+      uint16_t ph = p16[j];
+      float mo = m[j], vo = v[j];
+      one(ph, mo, vo, g[j]);
+      m[j] = mo;
+      v[j] = vo;
+      p16[j] = ph;
     }
   }
 }

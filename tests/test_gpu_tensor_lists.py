@@ -1,5 +1,5 @@
-"""AdamW and the clip over lists of tensors: counts around the 64 tensors of a launch, sizes around the 4096 elements of
-a workgroup and the four-element vectors, empty tensors, buffers off alignment and buffers that are listed twice (each
+"""AdamW and the clip over lists of tensors: counts around the 64 tensors of a launch, sizes around the 512 and 4096
+elements of a workgroup and the four-element vectors, empty tensors, buffers off alignment and buffers that are listed twice (each
 listing acts, in order), bit-identical to the oracle."""
 
 import numpy as np
@@ -12,7 +12,7 @@ import paper_2609_17380_amd.inputs as I
 from gpu_util import DEV, assert_bits, host_f32, host_u16
 
 pytestmark = pytest.mark.gpu
-EDGES = [0, 1, 3, 4, 1023, 1025, 4095, 4096, 4097, 4099, 8193]
+EDGES = [0, 1, 3, 4, 511, 512, 513, 1025, 4095, 4096, 4097, 4099, 8193]
 
 
 def place(host, dtype, off):
