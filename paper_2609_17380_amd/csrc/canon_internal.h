@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "tensor_batches.h"
+
 namespace canon {
 
 enum { KMODE_FULL = 0, KMODE_TRAIL = 1, KMODE_LEAD = 2 };
@@ -84,63 +86,9 @@ hipError_t qlinear_bwd_launch(int64_t T, int64_t N, int64_t K, const void* dy, i
                               hipStream_t s);
 int gemm_max_levels();
 
-// Kernels over a list of tensors take up to kBatchTensors of them per launch, as a table in the kernel arguments
-// (4 KiB at most).  Empty tensors are left out; a tensor owns ceil(size / unit) consecutive workgroups, start[j]
-// being the first of entry j (unused entries 0xFFFFFFFF).
-constexpr int kBatchTensors = 64;
-// the entry of this workgroup: one ballot, a lane per entry
-__device__ __forceinline__ int batch_tensor(const uint32_t (&start)[kBatchTensors]) {
-  return __popcll(__ballot(start[threadIdx.x & 63] <= blockIdx.x)) - 1;
-}
-// The buffers of one launch, sorted; a list may name a buffer twice (it is then updated twice, in order), so a tensor
-// that touches one of these starts the next launch.
-struct BufferSet {
-  uintptr_t lo[4 * kBatchTensors], hi[4 * kBatchTensors];
-  int n = 0;
-  bool add(const void* p, int64_t bytes) {  // false: overlaps a buffer of the set (not added)
-    const uintptr_t a = (uintptr_t)p, b = a + (uintptr_t)bytes;
-    int i = n;
-    while (i > 0 && lo[i - 1] >= a) --i;
-    if ((i > 0 && hi[i - 1] > a) || (i < n && lo[i] < b)) return false;
-    for (int k = n; k > i; --k) {
-      lo[k] = lo[k - 1];
-      hi[k] = hi[k - 1];
-    }
-    lo[i] = a;
-    hi[i] = b;
-    ++n;
-    return true;
-  }
-};
-// add(set, t) enters tensor t's buffers and says whether they were disjoint from those already there
-template <class Add, class Put, class Run>
-hipError_t for_tensor_batches(int64_t nt, const int64_t* sizes, int64_t unit, uint32_t (&start)[kBatchTensors],
-                              Add add, Put put, Run run) {
-  BufferSet used;
-  int j = 0;
-  int64_t blocks = 0;
-  auto flush = [&]() {
-    for (int i = j; i < kBatchTensors; ++i) start[i] = 0xFFFFFFFFu;
-    const hipError_t e = j > 0 ? run((uint32_t)blocks) : hipSuccess;
-    j = 0;
-    blocks = 0;
-    used.n = 0;
-    return e;
-  };
-  for (int64_t t = 0; t < nt; ++t) {
-    if (sizes[t] == 0) continue;
-    const int64_t b = (sizes[t] + unit - 1) / unit;
-    if (j == kBatchTensors || (j > 0 && blocks + b > 0x7FFFFFFF) || !add(used, t)) {
-      const hipError_t e = flush();
-      if (e != hipSuccess) return e;
-      add(used, t);
-    }
-    start[j] = (uint32_t)blocks;
-    put(j, t);
-    blocks += b;
-    ++j;
-  }
-  return flush();
+// The entry of unit `unit` in a launch over a list of tensors (tensor_batches.h): one ballot, a lane per entry.
+__device__ __forceinline__ int batch_tensor(const uint32_t (&start)[kBatchTensors], uint32_t unit) {
+  return __popcll(__ballot(start[threadIdx.x & 63] <= unit)) - 1;
 }
 
 // norm.hip: global gradient norm, clip coefficient, spike decision (R15)

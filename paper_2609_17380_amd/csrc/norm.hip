@@ -220,8 +220,10 @@ __global__ __launch_bounds__(64 * kFinalWaves) void gnorm_final_kernel(
 }
 
 // g <- RN(g * coef) when coef < 1: up to kBatchTensors tensors per launch, kClipBlock elements of one tensor per
-// workgroup, any alignment (110 M elements in 51 tensors: 291 us as a launch per tensor, 144 in one).
+// unit of work, any alignment (110 M elements in 51 tensors: 291 us as a launch per tensor, 144 in one).
 constexpr int kClipBlock = 4096;
+constexpr int64_t kClipUnits = 0x7FFFFFFF;  // per launch: 32-bit counts with room for one stride past the last
+constexpr uint32_t kClipGrid = kGridMax;    // workgroups, which walk the units with the grid as their stride
 struct ClipTable {
   float* g[kBatchTensors];
   int64_t n[kBatchTensors];
@@ -230,25 +232,28 @@ struct ClipTable {
 struct __attribute__((packed, aligned(4))) ClipF4 {
   float f[4];
 };
-__global__ __launch_bounds__(256) void clip_scale_kernel(ClipTable tab, const float* __restrict__ coef) {
+__global__ __launch_bounds__(kBatchThreads) void clip_scale_kernel(ClipTable tab, uint32_t units,
+                                                                   const float* __restrict__ coef) {
   const float c = *coef;
   if (!(c < 1.0f)) return;
-  const int t = batch_tensor(tab.start);
-  float* __restrict__ g = tab.g[t];
-  const int64_t n = tab.n[t], i0 = (int64_t)(blockIdx.x - tab.start[t]) * kClipBlock + 4 * threadIdx.x;
-  if (i0 + kClipBlock - 1024 + 4 <= n) {  // all four vectors: loads in flight before the stores
-    ClipF4 x[kClipBlock / 1024];
+  for (uint32_t unit = blockIdx.x; unit < units; unit += gridDim.x) {
+    const int t = batch_tensor(tab.start, unit);
+    float* __restrict__ g = tab.g[t];
+    const int64_t n = tab.n[t], i0 = (int64_t)(unit - tab.start[t]) * kClipBlock + 4 * threadIdx.x;
+    if (i0 + kClipBlock - 1024 + 4 <= n) {  // all four vectors: loads in flight before the stores
+      ClipF4 x[kClipBlock / 1024];
 #pragma unroll
-    for (int q = 0; q < kClipBlock / 1024; ++q) x[q] = *reinterpret_cast<const ClipF4*>(g + i0 + 1024 * q);
+      for (int q = 0; q < kClipBlock / 1024; ++q) x[q] = *reinterpret_cast<const ClipF4*>(g + i0 + 1024 * q);
 #pragma unroll
-    for (int q = 0; q < kClipBlock / 1024; ++q) {
+      for (int q = 0; q < kClipBlock / 1024; ++q) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) x[q].f[e] = x[q].f[e] * c;
-      *reinterpret_cast<ClipF4*>(g + i0 + 1024 * q) = x[q];
+        for (int e = 0; e < 4; ++e) x[q].f[e] = x[q].f[e] * c;
+        *reinterpret_cast<ClipF4*>(g + i0 + 1024 * q) = x[q];
+      }
+    } else {
+      for (int q = 0; q < kClipBlock / 1024; ++q)
+        for (int64_t j = i0 + 1024 * q; j < i0 + 1024 * q + 4 && j < n; ++j) g[j] = g[j] * c;
     }
-  } else {
-    for (int q = 0; q < kClipBlock / 1024; ++q)
-      for (int64_t j = i0 + 1024 * q; j < i0 + 1024 * q + 4 && j < n; ++j) g[j] = g[j] * c;
   }
 }
 
@@ -315,15 +320,18 @@ hipError_t norm_tables_launch(int64_t nt, const int64_t* sizes, float* const* gr
 hipError_t clip_scale_launch(int64_t nt, const int64_t* sizes, float* const* g, const float* coef, hipStream_t s) {
   ClipTable tab;
   return for_tensor_batches(
-      nt, sizes, kClipBlock, tab.start, [&](BufferSet& u, int64_t t) { return u.add(g[t], 4 * sizes[t]); },
+      nt, sizes, kClipBlock, kClipUnits, kClipUnits * kClipBlock, tab.start,
+      [&](int64_t t, auto f) { f(g[t], 4 * sizes[t]); },
       [&](int j, int64_t t) {
         tab.g[j] = g[t];
         tab.n[j] = sizes[t];
       },
-      [&](uint32_t blocks) {
-        hipLaunchKernelGGL(clip_scale_kernel, dim3(blocks), dim3(256), 0, s, tab, coef);
+      [&](int, uint32_t units) {
+        hipLaunchKernelGGL(clip_scale_kernel, dim3(units < kClipGrid ? units : kClipGrid), dim3(kBatchThreads), 0, s,
+                           tab, units, coef);
         return hipGetLastError();
-      });
+      },
+      [](int64_t) { return hipErrorInvalidValue; });  // (2^43 elements, beyond the entry points' 2^40)
 }
 
 }  // namespace canon

@@ -284,6 +284,8 @@ struct AdamWK {
 // ramps up and drains on its own), 453 us in one; one tensor of 1.2e9: 5203 -> 4899 us.  With 1 or 4 elements per
 // thread 507 / 480 and 5616 / 5226 us, with four 16-byte vectors per thread 489 and 5424.
 constexpr int kAdamWBlock = 512;
+// A tensor with more workgroups than a launch takes goes by itself, its grid striding over it.
+constexpr int64_t kAdamWLarge = (int64_t)kGridMax * kAdamWBlock + 1;
 struct AdamWTable {
   uint16_t* p[kBatchTensors];
   float* m[kBatchTensors];
@@ -293,20 +295,25 @@ struct AdamWTable {
   uint64_t decay;                  // bit t: tensor t decays
   uint32_t start[kBatchTensors];   // first workgroup of each tensor; unused entries 0xFFFFFFFF
 };
-__global__ __launch_bounds__(256) void adamw_kernel(AdamWTable tab, AdamWK k, const float* __restrict__ gscale,
-                                                    const int32_t* __restrict__ skip) {
-  if (skip && *skip) return;
-  const int t = batch_tensor(tab.start);
-  const float c = gscale ? *gscale : 1.0f;
-  const bool clip = c < 1.0f, decay = (tab.decay >> t) & 1;
-  uint16_t* __restrict__ p16 = tab.p[t];
-  float* __restrict__ m = tab.m[t];
-  float* __restrict__ v = tab.v[t];
-  const float* __restrict__ g = tab.g[t];
-  const int64_t n = tab.n[t], i0 = (int64_t)(blockIdx.x - tab.start[t]) * kAdamWBlock;
+struct AdamWOne {
+  uint16_t* p;
+  float* m;
+  float* v;
+  const float* g;
+  int64_t n;
+  bool decay;
+};
+
+// the E * kBatchThreads elements of tensor T from i0 on, loaded together
+template <int E>
+__device__ __forceinline__ void adamw_unit(const AdamWOne& T, int64_t i0, const AdamWK& k, bool clip, float c) {
+  uint16_t* __restrict__ p16 = T.p;
+  float* __restrict__ m = T.m;
+  float* __restrict__ v = T.v;
+  const float* __restrict__ g = T.g;
   auto one = [&](uint16_t& ph, float& mo, float& vo, float gi) __attribute__((always_inline)) {
     float p = bf16_to_f32(ph);
-    if (decay) p = p * k.decay_factor;
+    if (T.decay) p = p * k.decay_factor;
     if (clip) gi = gi * c;
     float m1 = k.beta1 * mo;
     float m2 = k.omb1 * gi;
@@ -325,27 +332,26 @@ __global__ __launch_bounds__(256) void adamw_kernel(AdamWTable tab, AdamWK k, co
     vo = vi;
     ph = f32_to_bf16(p);
   };
-  constexpr int E = kAdamWBlock / 256;  // loads in flight before the arithmetic
   const int64_t i0t = i0 + threadIdx.x;
-  if (i0 + kAdamWBlock <= n) {
+  if (i0 + E * kBatchThreads <= T.n) {
     uint16_t ph[E];
     float mo[E], vo[E], gi[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      ph[e] = p16[i0t + 256 * e];
-      mo[e] = m[i0t + 256 * e];
-      vo[e] = v[i0t + 256 * e];
-      gi[e] = g[i0t + 256 * e];
+      ph[e] = p16[i0t + kBatchThreads * e];
+      mo[e] = m[i0t + kBatchThreads * e];
+      vo[e] = v[i0t + kBatchThreads * e];
+      gi[e] = g[i0t + kBatchThreads * e];
     }
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       one(ph[e], mo[e], vo[e], gi[e]);
-      m[i0t + 256 * e] = mo[e];
-      v[i0t + 256 * e] = vo[e];
-      p16[i0t + 256 * e] = ph[e];
+      m[i0t + kBatchThreads * e] = mo[e];
+      v[i0t + kBatchThreads * e] = vo[e];
+      p16[i0t + kBatchThreads * e] = ph[e];
     }
   } else {
-    for (int64_t j = i0t; j < n; j += 256) {
+    for (int64_t j = i0t; j < T.n; j += kBatchThreads) {
       uint16_t ph = p16[j];
       float mo = m[j], vo = v[j];
       one(ph, mo, vo, g[j]);
@@ -356,16 +362,38 @@ __global__ __launch_bounds__(256) void adamw_kernel(AdamWTable tab, AdamWK k, co
   }
 }
 
+__global__ __launch_bounds__(kBatchThreads) void adamw_kernel(AdamWTable tab, AdamWK k,
+                                                              const float* __restrict__ gscale,
+                                                              const int32_t* __restrict__ skip) {
+  if (skip && *skip) return;
+  const float c = gscale ? *gscale : 1.0f;
+  const int t = batch_tensor(tab.start, blockIdx.x);
+  const AdamWOne T{tab.p[t], tab.m[t], tab.v[t], tab.g[t], tab.n[t], ((tab.decay >> t) & 1) != 0};
+  adamw_unit<kAdamWBlock / kBatchThreads>(T, (int64_t)(blockIdx.x - tab.start[t]) * kAdamWBlock, k, c < 1.0f, c);
+}
+
+// one tensor, the grid as the stride
+__global__ __launch_bounds__(kBatchThreads) void adamw_one_kernel(AdamWOne T, AdamWK k,
+                                                                  const float* __restrict__ gscale,
+                                                                  const int32_t* __restrict__ skip) {
+  if (skip && *skip) return;
+  const float c = gscale ? *gscale : 1.0f;
+  for (int64_t i0 = (int64_t)blockIdx.x * kAdamWBlock; i0 < T.n; i0 += (int64_t)gridDim.x * kAdamWBlock)
+    adamw_unit<kAdamWBlock / kBatchThreads>(T, i0, k, c < 1.0f, c);
+}
+
 hipError_t adamw_launch(int64_t nt, const int64_t* sizes, uint16_t* const* p, float* const* m, float* const* v,
                         const float* const* g, const uint8_t* decay, const float* c9, const float* gscale,
                         const int32_t* skip_flag, hipStream_t s) {
   AdamWK k{c9[0], c9[1], c9[2], c9[3], c9[4], c9[5], c9[6], c9[7], c9[8]};
   AdamWTable tab;
   return for_tensor_batches(
-      nt, sizes, kAdamWBlock, tab.start,
-      [&](BufferSet& u, int64_t t) {
-        return u.add(p[t], 2 * sizes[t]) & u.add(m[t], 4 * sizes[t]) & u.add(v[t], 4 * sizes[t]) &
-               u.add(g[t], 4 * sizes[t]);
+      nt, sizes, kAdamWBlock, kGridMax, kAdamWLarge, tab.start,
+      [&](int64_t t, auto f) {
+        f(p[t], 2 * sizes[t]);
+        f(m[t], 4 * sizes[t]);
+        f(v[t], 4 * sizes[t]);
+        f(g[t], 4 * sizes[t]);
       },
       [&](int j, int64_t t) {
         tab.p[j] = p[t];
@@ -376,8 +404,13 @@ hipError_t adamw_launch(int64_t nt, const int64_t* sizes, uint16_t* const* p, fl
         if (j == 0) tab.decay = 0;
         tab.decay |= (uint64_t)(decay[t] != 0) << j;
       },
-      [&](uint32_t blocks) {
-        hipLaunchKernelGGL(adamw_kernel, dim3(blocks), dim3(256), 0, s, tab, k, gscale, skip_flag);
+      [&](int, uint32_t blocks) {
+        hipLaunchKernelGGL(adamw_kernel, dim3(blocks), dim3(kBatchThreads), 0, s, tab, k, gscale, skip_flag);
+        return hipGetLastError();
+      },
+      [&](int64_t t) {
+        const AdamWOne T{p[t], m[t], v[t], g[t], sizes[t], decay[t] != 0};
+        hipLaunchKernelGGL(adamw_one_kernel, dim3(kGridMax), dim3(kBatchThreads), 0, s, T, k, gscale, skip_flag);
         return hipGetLastError();
       });
 }

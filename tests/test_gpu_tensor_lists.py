@@ -71,3 +71,22 @@ def test_clip_lists(count, off):
         if i == 0 and coef < 1:
             want = want * coef
         assert_bits(host_f32(dg[i]), want, f"g{i}")
+
+
+@pytest.mark.parametrize("sizes", [[(1 << 33) + 5], [1 << 32, (1 << 32) + 777, 1000]])
+def test_adamw_more_elements_than_one_grid_takes(sizes):
+    # a workgroup of 256 threads per 512 elements: above 8.59e9 elements a launch would have 2^32 threads or more
+    print(f"adamw {sizes}", flush=True)
+    k = I.adamw_constants()
+    one = [np.array([0x3F80], np.uint16)], [np.array([0.5], np.float32)], [np.array([0.25], np.float32)]
+    oracle.adamw(*one, [np.array([2.0], np.float32)], [True], oracle.AdamWConsts(*k))
+    p = [torch.full((n,), 1.0, dtype=torch.bfloat16, device=DEV) for n in sizes]
+    m, v, g = ([torch.full((n,), x, dtype=torch.float32, device=DEV) for n in sizes] for x in (0.5, 0.25, 2.0))
+    C.adamw(p, m, v, g, [True] * len(sizes), C.AdamWConsts(*k))
+    torch.cuda.synchronize()
+    for ts, want in zip((p, m, v), one):
+        for t in ts:
+            assert_bits((host_u16 if t.dtype == torch.bfloat16 else host_f32)(t[-1:]), want[0], "last element")
+            assert int(t.min() == t.max()) == 1
+    del p, m, v, g, ts, t
+    torch.cuda.empty_cache()
