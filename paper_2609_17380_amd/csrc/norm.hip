@@ -220,10 +220,13 @@ __global__ __launch_bounds__(64 * kFinalWaves) void gnorm_final_kernel(
 }
 
 // g <- RN(g * coef) when coef < 1: up to kBatchTensors tensors per launch, kClipBlock elements of one tensor per
-// unit of work, any alignment (110 M elements in 51 tensors: 291 us as a launch per tensor, 144 in one).
+// unit of work, any alignment.  110 M elements in 51 tensors, norm and clip: 379 us as a launch per tensor, 200 in one.
+// The grid is bounded because every workgroup that finds no clip to do still has to start: 1.28e9 elements in one
+// tensor, norm and idle clip 888 us with a workgroup per unit, 828 with kClipGrid; a clip that acts 2650 and 2708
+// (16384 workgroups: 818 and 2801).
 constexpr int kClipBlock = 4096;
 constexpr int64_t kClipUnits = 0x7FFFFFFF;  // per launch: 32-bit counts with room for one stride past the last
-constexpr uint32_t kClipGrid = kGridMax;    // workgroups, which walk the units with the grid as their stride
+constexpr uint32_t kClipGrid = 65536;       // workgroups, which walk the units with the grid as their stride
 struct ClipTable {
   float* g[kBatchTensors];
   int64_t n[kBatchTensors];

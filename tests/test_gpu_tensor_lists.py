@@ -73,6 +73,21 @@ def test_clip_lists(count, off):
         assert_bits(host_f32(dg[i]), want, f"g{i}")
 
 
+def test_clip_walks_its_units():
+    # more units of 4096 elements than workgroups (65536), in tensors whose borders fall on any stride
+    sizes = [3, (1 << 28) + 5, 4097, (1 << 27) + 4096, 0, 9]
+    print(f"clip {sizes}", flush=True)
+    g = [torch.full((n,), 0.5, dtype=torch.float32, device=DEV) for n in sizes]
+    norm = torch.empty(1, dtype=torch.float32, device=DEV)
+    ws = torch.empty(C.clip_grad_norm_workspace_bytes(g), dtype=torch.uint8, device=DEV)
+    C.clip_grad_norm(g, C.make_clip(1.0, float("inf"), 0, norm), ws)
+    torch.cuda.synchronize()
+    want = np.float32(0.5) * (np.float32(1.0) / (host_f32(norm)[0] + np.float32(1e-6)))
+    for t in g:
+        if t.numel():
+            assert np.float32(t.min().item()) == want and np.float32(t.max().item()) == want
+
+
 @pytest.mark.parametrize("sizes", [[(1 << 33) + 5], [1 << 32, (1 << 32) + 777, 1000]])
 def test_adamw_more_elements_than_one_grid_takes(sizes):
     # a workgroup of 256 threads per 512 elements: above 8.59e9 elements a launch would have 2^32 threads or more
