@@ -280,12 +280,16 @@ struct AdamWK {
 
 // One launch updates up to kBatchTensors tensors: their table travels in the kernel arguments, a workgroup takes
 // kAdamWBlock consecutive elements of one tensor, two per thread, 256 apart and loaded together.  Bound: HBM, 24 bytes
-// per parameter.  110 M parameters in 51 tensors: 622 us as one launch per tensor (one element per thread; each launch
-// ramps up and drains on its own), 453 us in one; one tensor of 1.2e9: 5203 -> 4899 us.  With 1 or 4 elements per
-// thread 507 / 480 and 5616 / 5226 us, with four 16-byte vectors per thread 489 and 5424.
+// per parameter.  110 M parameters in 51 tensors: 603 us as one launch per tensor (one element per thread; each launch
+// ramps up and drains on its own), 433 us in one; with 1 or 4 elements per thread 507 / 480, with four 16-byte vectors
+// per thread 489.
 constexpr int kAdamWBlock = 512;
-// A tensor with more workgroups than a launch takes goes by itself, its grid striding over it.
-constexpr int64_t kAdamWLarge = (int64_t)kGridMax * kAdamWBlock + 1;
+// A tensor of kAdamWLarge elements or more, and one that is alone in its launch, goes without a table, whose look-up
+// stands before every load: 2^28 elements 1169 us with the table, 1078 without; 200 M 822 and 796; 2^18 3.1 and 2.8.
+// Large ones take one element per thread (two: 2^28 in 1190 us), two blocks of 256 per workgroup one after the other,
+// which halves the workgroups that a skipped update starts: 1.28e9 elements with one block 4983 us and 1053 skipped,
+// two 5156 and 528, four 5331 and 265; the same tensor in the table 5396 and 528.
+constexpr int64_t kAdamWLarge = int64_t(1) << 25;
 struct AdamWTable {
   uint16_t* p[kBatchTensors];
   float* m[kBatchTensors];
@@ -372,14 +376,18 @@ __global__ __launch_bounds__(kBatchThreads) void adamw_kernel(AdamWTable tab, Ad
   adamw_unit<kAdamWBlock / kBatchThreads>(T, (int64_t)(blockIdx.x - tab.start[t]) * kAdamWBlock, k, c < 1.0f, c);
 }
 
-// one tensor, the grid as the stride
+// one tensor, B blocks of E * kBatchThreads elements per workgroup; grid strides beyond kGridMax workgroups
+template <int E, int B>
 __global__ __launch_bounds__(kBatchThreads) void adamw_one_kernel(AdamWOne T, AdamWK k,
                                                                   const float* __restrict__ gscale,
                                                                   const int32_t* __restrict__ skip) {
   if (skip && *skip) return;
   const float c = gscale ? *gscale : 1.0f;
-  for (int64_t i0 = (int64_t)blockIdx.x * kAdamWBlock; i0 < T.n; i0 += (int64_t)gridDim.x * kAdamWBlock)
-    adamw_unit<kAdamWBlock / kBatchThreads>(T, i0, k, c < 1.0f, c);
+  constexpr int64_t U = E * kBatchThreads;
+  for (int64_t i1 = (int64_t)blockIdx.x * U * B; i1 < T.n; i1 += (int64_t)gridDim.x * U * B)
+#pragma unroll 1
+    for (int q = 0; q < B; ++q)
+      if (i1 + q * U < T.n) adamw_unit<E>(T, i1 + q * U, k, c < 1.0f, c);
 }
 
 hipError_t adamw_launch(int64_t nt, const int64_t* sizes, uint16_t* const* p, float* const* m, float* const* v,
@@ -387,6 +395,12 @@ hipError_t adamw_launch(int64_t nt, const int64_t* sizes, uint16_t* const* p, fl
                         const int32_t* skip_flag, hipStream_t s) {
   AdamWK k{c9[0], c9[1], c9[2], c9[3], c9[4], c9[5], c9[6], c9[7], c9[8]};
   AdamWTable tab;
+#define CANON_ADAMW_ONE(E, B)                                                                                   \
+  do {                                                                                                          \
+    const int64_t blocks = (T.n + E * B * kBatchThreads - 1) / (E * B * kBatchThreads);                         \
+    hipLaunchKernelGGL((adamw_one_kernel<E, B>), dim3((unsigned)(blocks < kGridMax ? blocks : kGridMax)),       \
+                       dim3(kBatchThreads), 0, s, T, k, gscale, skip_flag);                                     \
+  } while (0)
   return for_tensor_batches(
       nt, sizes, kAdamWBlock, kGridMax, kAdamWLarge, tab.start,
       [&](int64_t t, auto f) {
@@ -404,15 +418,22 @@ hipError_t adamw_launch(int64_t nt, const int64_t* sizes, uint16_t* const* p, fl
         if (j == 0) tab.decay = 0;
         tab.decay |= (uint64_t)(decay[t] != 0) << j;
       },
-      [&](int, uint32_t blocks) {
-        hipLaunchKernelGGL(adamw_kernel, dim3(blocks), dim3(kBatchThreads), 0, s, tab, k, gscale, skip_flag);
+      [&](int entries, uint32_t blocks) {
+        if (entries == 1) {  // one element per thread up to 4 workgroups per CU, two beyond (1 M: 5.4 against 4.9 us)
+          const AdamWOne T{tab.p[0], tab.m[0], tab.v[0], tab.g[0], tab.n[0], (tab.decay & 1) != 0};
+          if (T.n <= 4 * 256 * (int64_t)kBatchThreads) CANON_ADAMW_ONE(1, 1);
+          else CANON_ADAMW_ONE(2, 1);
+        } else {
+          hipLaunchKernelGGL(adamw_kernel, dim3(blocks), dim3(kBatchThreads), 0, s, tab, k, gscale, skip_flag);
+        }
         return hipGetLastError();
       },
       [&](int64_t t) {
         const AdamWOne T{p[t], m[t], v[t], g[t], sizes[t], decay[t] != 0};
-        hipLaunchKernelGGL(adamw_one_kernel, dim3(kGridMax), dim3(kBatchThreads), 0, s, T, k, gscale, skip_flag);
+        CANON_ADAMW_ONE(1, 2);
         return hipGetLastError();
       });
+#undef CANON_ADAMW_ONE
 }
 
 __global__ void set_nan_if_kernel(const int32_t* flag, float* x) {

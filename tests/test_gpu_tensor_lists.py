@@ -73,6 +73,27 @@ def test_clip_lists(count, off):
         assert_bits(host_f32(dg[i]), want, f"g{i}")
 
 
+@pytest.mark.parametrize("sizes", [[255], [257], [1 << 18], [(1 << 18) + 1], [(1 << 25) - 1], [1 << 25], [(1 << 25) + 257],
+                                   [1000, (1 << 25) + 769, 513]])
+def test_adamw_alone_and_large(sizes):
+    # a tensor alone in its launch (one element per thread up to 2^18, two beyond) and those of 2^25 elements, which go
+    # by themselves, two blocks of 256 per workgroup
+    print(f"adamw alone {sizes}", flush=True)
+    p = [I.normal_bf16((n,), i, 40, std=0.1) for i, n in enumerate(sizes)]
+    m, g = ([I.normal_f32((n,), i, s) for i, n in enumerate(sizes)] for s in (41, 43))
+    v = [np.square(x) for x in m]
+    k = I.adamw_constants()
+    dp = [place(x, torch.bfloat16, 1) for x in p]
+    dm, dv, dg = ([place(x, torch.float32, 1) for x in xs] for xs in (m, v, g))
+    oracle.adamw(p, m, v, g, [True] * len(sizes), oracle.AdamWConsts(*k))
+    C.adamw(dp, dm, dv, dg, [True] * len(sizes), C.AdamWConsts(*k))
+    torch.cuda.synchronize()
+    for i in range(len(sizes)):
+        assert_bits(host_u16(dp[i]), p[i], f"p{i}")
+        assert_bits(host_f32(dm[i]), m[i], f"m{i}")
+        assert_bits(host_f32(dv[i]), v[i], f"v{i}")
+
+
 def test_clip_walks_its_units():
     # more units of 4096 elements than workgroups (65536), in tensors whose borders fall on any stride
     sizes = [3, (1 << 28) + 5, 4097, (1 << 27) + 4096, 0, 9]
