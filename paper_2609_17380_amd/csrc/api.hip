@@ -682,18 +682,26 @@ HashPlan hash_plan(int64_t n, const int64_t* nbytes) {
   int64_t leaves = 0;
   for (int64_t t = 0; t < n; ++t) leaves += hash_leaf_count(nbytes[t]);
   hp.group = hash_leaf_group(leaves);
+  int64_t most = 0;  // groups of the smallest size
   for (int64_t t = 0; t < n; ++t) {
     hp.n_wg += (hash_leaf_count(nbytes[t]) + hp.group - 1) / hp.group;
+    most += (hash_leaf_count(nbytes[t]) + kHashLeafGroupMin - 1) / kHashLeafGroupMin;
   }
   auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
-  size_t o = 0;
-  hp.off_tens = o; o += up(sizeof(HashTensor) * (size_t)n);
-  hp.off_wgt = o; o += up(sizeof(int32_t) * (size_t)hp.n_wg);
-  hp.off_wgf = o; o += up(sizeof(int64_t) * (size_t)hp.n_wg);
-  hp.off_na = o; o += up(32 * (size_t)hp.n_wg);
-  hp.off_nb = o; o += up(32 * (size_t)hp.n_wg);
-  hp.off_td = o; o += up(32 * (size_t)n);
-  hp.bytes = o;
+  // The workspace is sized for the smallest groups whichever are taken, so that one that holds a state also holds
+  // every smaller one.
+  auto layout = [&](int64_t wgs) {
+    size_t o = 0;
+    hp.off_tens = o; o += up(sizeof(HashTensor) * (size_t)n);
+    hp.off_wgt = o; o += up(sizeof(int32_t) * (size_t)wgs);
+    hp.off_wgf = o; o += up(sizeof(int64_t) * (size_t)wgs);
+    hp.off_na = o; o += up(32 * (size_t)wgs);
+    hp.off_nb = o; o += up(32 * (size_t)wgs);
+    hp.off_td = o; o += up(32 * (size_t)n);
+    return o;
+  };
+  hp.bytes = layout(most);
+  layout(hp.n_wg);
   return hp;
 }
 

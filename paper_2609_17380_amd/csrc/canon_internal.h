@@ -74,7 +74,8 @@ struct HashTensor {
   int64_t nbytes, leaves, node_offset;  // node_offset: its first slot among the leaf groups' nodes
 };
 int64_t hash_leaf_count(int64_t nbytes);
-int64_t hash_leaf_group(int64_t total_leaves);  // leaves per workgroup, folded to one node
+constexpr int64_t kHashLeafGroupMin = 64;
+int64_t hash_leaf_group(int64_t total_leaves);  // leaves per workgroup, folded to one node: 64 or 256
 hipError_t hash_launch(int64_t n_tensors, const HashTensor* tens_dev, int64_t group, int64_t n_wg,
                        const int32_t* wg_tensor, const int64_t* wg_first, uint32_t* node_a, uint32_t* node_b,
                        uint32_t* tensor_digests, uint8_t* out, hipStream_t s);

@@ -349,9 +349,9 @@ __global__ __launch_bounds__(64) void hash_state_kernel(int64_t n_tensors, const
     for (int i = 0; i < 4; ++i) out[4 * k + i] = (uint8_t)(s[k] >> (24 - 8 * i));
 }
 
-// Leaves per workgroup for a state of so many leaves in all (a fixed line, so that workspace sizes do not depend on the
+// Leaves per workgroup for a state of so many leaves in all (a fixed line, the same on every
 // device): from one and a half groups of 256 per CU on, the four-pair workgroups are the faster ones.
-int64_t hash_leaf_group(int64_t total_leaves) { return total_leaves >= 256 * 384 ? 256 : 64; }
+int64_t hash_leaf_group(int64_t total_leaves) { return total_leaves >= 256 * 384 ? 256 : kHashLeafGroupMin; }
 
 int64_t hash_leaf_count(int64_t nbytes) {
   const int64_t nb = (nbytes + 63) / 64;
@@ -362,7 +362,7 @@ int64_t hash_leaf_count(int64_t nbytes) {
 hipError_t hash_launch(int64_t n_tensors, const HashTensor* tens_dev, int64_t group, int64_t n_wg,
                        const int32_t* wg_tensor, const int64_t* wg_first, uint32_t* node_a, uint32_t* node_b,
                        uint32_t* tensor_digests, uint8_t* out, hipStream_t s) {
-  if (n_wg > 0 && group == 64)
+  if (n_wg > 0 && group == kHashLeafGroupMin)
     hipLaunchKernelGGL(hash_leaves_kernel<1>, dim3((unsigned)n_wg), dim3(128), 0, s, tens_dev, wg_tensor, wg_first,
                        node_a);
   else if (n_wg > 0)

@@ -34,6 +34,24 @@ def test_workspace_queries_without_gpu():
     assert C.step_workspace_bytes(bad, plan) == 0
 
 
+def test_state_hash_workspace_grows_with_the_state():
+    # the leaf pass takes wider groups from 98304 leaves of 64 KB in all on; a workspace for a state must still hold
+    # every smaller one
+    import paper_2609_17380_amd.canon as C
+    lib, leaf = C.lib(), 64 * 1024
+
+    def need(sizes):
+        return lib.canon_state_hash_workspace_bytes(len(sizes), (ctypes.c_int64 * len(sizes))(*sizes))
+
+    last = 0
+    for leaves in (1, 64, 65, 50000, 98303, 98304, 98305, 120000, 400000):
+        assert need([leaf * leaves]) >= last
+        last = need([leaf * leaves])
+    for t in range(1, 40):  # one tensor more across the line
+        assert need([leaf * 4096] * (t + 1)) >= need([leaf * 4096] * t)
+        assert need([leaf * 4096] * t + [1]) >= need([leaf * 4096] * t)
+
+
 def test_oracle_and_library_share_no_source():
     lib_src = open(os.path.join(ROOT, "paper_2609_17380_amd", "csrc", "canon_dev.h")).read()
     orc = open(os.path.join(ROOT, "oracle", "canon_ref.c")).read()
