@@ -35,6 +35,8 @@
 // other outputs leave them unwritten.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+
 #include "canon_dev.h"
 #include "canon_internal.h"
 
@@ -934,11 +936,16 @@ static hipError_t launch_maxl(const GemmArgs& g, int64_t cus, hipStream_t s) {
 
 int gemm_max_levels() { return 12; }
 
+// Asked of the runtime once per device (a 128 x 128 x 256 call's host part: 3.58 us with the query in every call, 3.45
+// without).
 int64_t device_cus() {
+  static std::atomic<int> known[64];
   int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-    cus = 256;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  const bool keep = dev >= 0 && dev < 64;
+  if (keep && (cus = known[dev].load(std::memory_order_relaxed)) > 0) return cus;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+  if (keep) known[dev].store(cus, std::memory_order_relaxed);
   return cus;
 }
 
