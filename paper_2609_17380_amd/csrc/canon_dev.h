@@ -192,11 +192,16 @@ __device__ __forceinline__ void quant_pack(const float (&v)[N], float s, float r
   }
 #pragma unroll
   for (int j = 0; j < N / 4; ++j) w[j] ^= 0x80808080u;
+  // Most often one value of one lane: the others' quotients are passed over (all N redone, the wavefront that had one
+  // made a small launch wait: 33 x 2048 bf16 with a step per row 3.0 us, now 2.6; 2048 x 2048 4.75 and 4.2).
   if (exact) {
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-      const uint32_t b = (uint8_t)quant1(v[j], s);
-      w[j >> 2] = (j & 3) ? w[j >> 2] | (b << (8 * (j & 3))) : b;
+      const float t = v[j] * rs;
+      if (!recip || !(fabsf(t - __builtin_rintf(t)) < 0.5f - 0x1p-15f)) {
+        const uint32_t b = (uint8_t)quant1(v[j], s), at = 8 * (j & 3);
+        w[j >> 2] = (w[j >> 2] & ~(0xFFu << at)) | (b << at);
+      }
     }
   }
 }
