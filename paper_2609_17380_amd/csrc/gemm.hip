@@ -568,7 +568,14 @@ __global__ __launch_bounds__(CF::NT, CF::OCC * CF::NW / 4) void gemm_mfma_kernel
 
   // store: register v of lane l -> row Mfma::orow, column Mfma::ocol of the wavefront's block
   const int64_t crow0 = lrow0 + wr * WR, ccol0 = lcol0 + wc * 64;
-  auto mine = [&](int64_t i, int64_t j) { return i >= row0 && i < g.m && j >= col0 && j < g.n; };
+  // inside this tile (of a shifted tile only its own rows and columns), in 32-bit positions within the loaded one: 64-bit
+  // comparisons made short contractions 5% slower (4096 x 4096 x 32 30.8 against 28.9 us)
+  const int rlo = (int)(row0 - lrow0), rn = (int)(g.m - lrow0 < BM ? g.m - lrow0 : BM) - rlo;
+  const int clo = (int)(col0 - lcol0), cn = (int)(g.n - lcol0 < TBN ? g.n - lcol0 : TBN) - clo;
+  auto mine = [&](int v) {
+    return (uint32_t)(wr * WR + Mfma<V>::orow(v, lane) - rlo) < (uint32_t)rn &&
+           (uint32_t)(wc * 64 + Mfma<V>::ocol(v, lane) - clo) < (uint32_t)cn;
+  };
   if (g.epi == EPI_DS) {
     uint16_t* C = (uint16_t*)g.c + z1 * g.sc1 + z2 * g.sc2;
     const uint16_t* P = g.ds_p + z1 * g.ds_sp1 + z2 * g.ds_sp2;
@@ -577,7 +584,7 @@ __global__ __launch_bounds__(CF::NT, CF::OCC * CF::NW / 4) void gemm_mfma_kernel
     for (int v = 0; v < V; ++v) {
       const int64_t i = crow0 + Mfma<V>::orow(v, lane);
       const int64_t j = ccol0 + Mfma<V>::ocol(v, lane);
-      if (mine(i, j)) {
+      if (mine(v)) {
         uint16_t o = 0;
         if (j <= i && (g.ds_window == 0 || j > i - g.ds_window)) {
           const float t = r[v] - Dv[i];
@@ -596,7 +603,7 @@ __global__ __launch_bounds__(CF::NT, CF::OCC * CF::NW / 4) void gemm_mfma_kernel
     for (int v = 0; v < V; ++v) {
       const int64_t i = crow0 + Mfma<V>::orow(v, lane);
       const int64_t j = ccol0 + Mfma<V>::ocol(v, lane);
-      if (mine(i, j)) C[i * g.ldc + j] = R[i * g.ldres + j] + r[v];
+      if (mine(v)) C[i * g.ldc + j] = R[i * g.ldres + j] + r[v];
     }
     return;
   }
@@ -606,7 +613,7 @@ __global__ __launch_bounds__(CF::NT, CF::OCC * CF::NW / 4) void gemm_mfma_kernel
     for (int v = 0; v < V; ++v) {
       const int64_t i = crow0 + Mfma<V>::orow(v, lane);
       const int64_t j = ccol0 + Mfma<V>::ocol(v, lane);
-      if (mine(i, j)) {
+      if (mine(v)) {
         const float t = r[v] * g.epi_scale;
         C[i * g.ldc + j] = C[i * g.ldc + j] + t;
       }
@@ -617,7 +624,7 @@ __global__ __launch_bounds__(CF::NT, CF::OCC * CF::NW / 4) void gemm_mfma_kernel
   for (int v = 0; v < V; ++v) {
     const int64_t i = crow0 + Mfma<V>::orow(v, lane);
     const int64_t j = ccol0 + Mfma<V>::ocol(v, lane);
-    if (mine(i, j)) {
+    if (mine(v)) {
       if (g.out_bf16) {
         uint16_t* C = (uint16_t*)g.c + z1 * g.sc1 + z2 * g.sc2;
         C[i * g.ldc + j] = f32_to_bf16(r[v]);
