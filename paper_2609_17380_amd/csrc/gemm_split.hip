@@ -227,10 +227,10 @@ __global__ __launch_bounds__(64 * SW, 2) void gemm_split_kernel(GemmArgs g, uint
       }
     }
   }
-  auto real = [&](uint32_t c) {
-    if (!CZ) return true;
-    const uint32_t cl = c % spc;
-    return cl >= lb && cl < le;
+  // real chunks among the first c
+  auto reals = [&](uint32_t c) {
+    const uint32_t sg = g.kseg > 0 ? c / spc : 0u, cl = c - sg * spc;
+    return sg * (le - lb) + (cl < lb ? 0u : (cl < le ? cl : le) - lb);
   };
 
   uint32_t cnt[KB], first[KB];
@@ -294,8 +294,12 @@ __global__ __launch_bounds__(64 * SW, 2) void gemm_split_kernel(GemmArgs g, uint
   };
   auto next = [&](uint32_t q) {  // the next real local chunk after q, or n0
     ++q;
-    if (CZ)
-      while (q < n0 && !real(first[0] + q)) ++q;
+    if (CZ && q < n0) {
+      const uint32_t c = first[0] + q, cl = g.kseg > 0 ? c % spc : c;
+      if (lb >= le) q = n0;
+      else if (cl < lb) q += lb - cl;
+      else if (cl >= le) q += spc - cl + lb;  // the next segment's first
+    }
     return q < n0 ? q : n0;
   };
   // One chunk: local chunk qa, staged in buffer buf.  x holds the operands of qb, the next one: they are staged
@@ -333,8 +337,7 @@ __global__ __launch_bounds__(64 * SW, 2) void gemm_split_kernel(GemmArgs g, uint
     if (CZ) {
       steps = 0;
       for (uint32_t c0 = 0; c0 < nc; c0 += G) {
-        uint32_t k = 0;
-        for (uint32_t c = c0; c < c0 + G && c < nc; ++c) k += real(c) ? 1u : 0u;
+        const uint32_t k = reals(c0 + G < nc ? c0 + G : nc) - reals(c0);
         steps = k > steps ? k : steps;
       }
     }
@@ -445,6 +448,13 @@ hipError_t launch(const GemmArgs& g, int cfg, bool cz, hipStream_t s) {
 // (us): 256 x 256 (1, 4) 15 against 99; 100 x 1000 (1, 2) 21 against 100; 256 x 768 (1, 1) 32 against 100;
 // 512 x 1024 (2, 1) 57 against 101.  One step further, 1024 x 1024 in 256 tiles of 64 rows, it ties (97-110
 // against 101), and with two workgroups on a CU it loses (333 x 1555 (2, 1) 108 against 101).
+// Causal products of S queries (split against general, us; h heads of 64): P.V, S = 512, 8 heads (1, 1) 9.0 against 39;
+// S = 2048, 4 heads (2, 1) 35 against 138, with a window of 100 15 against 27; dK / dV, S = 2048, 4 heads (2, 1) 33
+// against 65, window 512 25 against 26, window 100 14 against 15; 4 query heads per key head, 16 heads (2, 1) 113 against
+// 254, window 20 29 against 49.  Only dK / dV of one head with a window that is short in a long sequence loses, where
+// the real chunks lie in one or two of the four ranges and the others push their +0: S = 4096, 2 heads 18.0 against
+// 15.0 (window 20), 30 against 29 (512), 45 against 43 (1024); S = 8192, 1 head 56 against 48 (1024).  With one row group
+// the split is the faster one there too (S = 4096, 1 head, window 20 9.9 against 14.5).
 int gemm_split_config(const GemmArgs& g, int64_t cus) {
   const int64_t lim = int64_t(1) << 30;  // operand elements: byte offsets below 2^32
   if (g.epi == EPI_DS || g.tri_lower || g.m < 16 || g.n < 16 || g.m > lim || g.n > lim || g.k < 8) return 0;
@@ -459,7 +469,8 @@ int gemm_split_config(const GemmArgs& g, int64_t cus) {
     if (nc >= 2 && fits(16, 32)) return 16 + 2;
   }
   if (fits(16, 64)) return 16 + 1;
-  if (fits(32, 64)) return 32 + 1;
+  const bool short_window = g.kmode == KMODE_LEAD && g.kseg == 0 && g.kwin > 0 && 4 * g.kwin <= g.k && nc >= 128;
+  if (fits(32, 64) && !short_window) return 32 + 1;
   return 0;
 }
 
