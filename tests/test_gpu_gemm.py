@@ -1,5 +1,6 @@
 """canon_gemm against the oracle: bit for bit at small shapes (all layouts, ragged tiles, many chunk
-counts) and on sampled outputs at the 1B decoder's full GEMM shapes."""
+counts) and on sampled outputs at the 1B decoder's full GEMM shapes.  Outputs of these small shapes run on the kernel that
+splits K over wavefronts; test_gpu_gemm_general.py has the same coverage of the general kernel."""
 import numpy as np
 import pytest
 import torch
@@ -45,8 +46,8 @@ def test_layouts_and_ragged_shapes(m, n, k, ta, tb):
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("k", [2048, 6144, 6144 + 32, 8192, 16384, 16384 + 96, 50304, 128256])
 def test_deep_folds(k, ta, tb):
-    # chunk counts 64, 192, 193, 256, 512, 515, 1572, 4008: every fold depth the steps use (stack depths 7, 9,
-    # 11 and 12), in every operand layout
+    # chunk counts 64, 192, 193, 256, 512, 515, 1572, 4008 of every contraction the steps use, in every operand layout:
+    # ranges of 2 to 256 chunks per wavefront
     print(f"gemm fold depth k={k} ta={ta} tb={tb}", flush=True)
     m, n = 70, 130
     a, b = operands(m, n, k, ta, tb, 4)
@@ -56,8 +57,7 @@ def test_deep_folds(k, ta, tb):
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("k", [64, 96, 2048, 2080, 6144, 8192, 16384 + 32, 50304, 128256])
 def test_whole_tiles_every_depth(k, ta, tb):
-    # whole 64 x 128 tiles (the unchecked 16-byte load path of every chunk), even and odd chunk counts, every
-    # stack depth, every layout
+    # rows and columns in whole tiles, even and odd chunk counts, ranges of 1 to 128 chunks per wavefront, every layout
     print(f"gemm whole tiles 128x256x{k} ta={ta} tb={tb}", flush=True)
     m, n = 128, 256
     a, b = operands(m, n, k, ta, tb, 8)
