@@ -184,13 +184,13 @@ __global__ __launch_bounds__(64 * SW, 2) void gemm_split_kernel(GemmArgs g, uint
   constexpr int LOADA = RG > 1 ? 1 : KB, LOADB = 4 / RG;       // blocks each wavefront loads
   constexpr int PFLOATS = SW * 16 * 64;                        // the ranges' results
   __shared__ __attribute__((aligned(16))) float lds[RBUF * NBUF * S > PFLOATS ? RBUF * NBUF * S : PFLOATS];
-  // each XCD (every 8th workgroup) takes a contiguous run of tiles, row tiles fastest, so that its L2 holds a
-  // few column panels
-  const uint32_t per = gridDim.x >> 3;
-  const uint32_t tile = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
-  if (tile >= tiles) return;
+  // each XCD (every 8th workgroup) takes a contiguous run of the batch's tiles, row tiles fastest, so that its L2 holds
+  // a few column panels or matrices (dealt by matrix, a batch of 40 with 4 tiles each had work for four of the XCDs)
+  const uint32_t at = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const uint32_t z = at / tiles, tile = at - z * tiles;
+  if (z >= (uint32_t)g.batch) return;
   const uint32_t tn = tile / tiles_m, tm = tile - tn * tiles_m;
-  const uint32_t nb2 = (uint32_t)g.nb2, z1 = blockIdx.z / nb2, z2 = blockIdx.z - z1 * nb2;
+  const uint32_t nb2 = (uint32_t)g.nb2, z1 = z / nb2, z2 = z - z1 * nb2;
   const uint16_t* A = g.a + z1 * g.sa1 + z2 * g.sa2;
   const uint16_t* B = g.b + z1 * g.sb1 + (g.b_group > 1 ? z2 / (uint32_t)g.b_group : z2) * g.sb2;
   const uint32_t m = (uint32_t)g.m, n = (uint32_t)g.n, K = (uint32_t)g.k, nc = (K + KC - 1) / KC;
@@ -427,7 +427,7 @@ hipError_t launch(const GemmArgs& g, int cfg, bool cz, hipStream_t s) {
   const uint32_t tiles = tm * tn, nc = (uint32_t)((g.k + KC - 1) / KC);
   uint32_t G = 1;
   while (G * (SW / rg) * kb < nc) G <<= 1;
-  const dim3 grid((tiles + 7) / 8 * 8, 1, (unsigned)g.batch), block(64 * SW);
+  const dim3 grid((unsigned)((tiles * g.batch + 7) / 8 * 8)), block(64 * SW);  // (at most a workgroup per CU)
 #define CANON_SPLIT(RG, KB, CZ) \
   hipLaunchKernelGGL((gemm_split_kernel<TA, TB, RG, KB, CZ>), grid, block, 0, s, g, tm, tiles, G)
   if (cz) {

@@ -9,6 +9,7 @@ import adversarial as ADV
 import oracle
 import paper_2609_17380_amd.canon as C
 import paper_2609_17380_amd.inputs as I
+from gemm_rule import split_config
 from gpu_util import DEV, assert_bits, dev_bf16, host_f32
 
 pytestmark = pytest.mark.gpu
@@ -94,3 +95,20 @@ def test_batched_split():
     torch.cuda.synchronize()
     for z in range(bt):
         assert_bits(host_f32(c[z]), oracle.gemm(a[z], b[z], False, True), f"batch {z}")
+
+
+@pytest.mark.parametrize("ta,tb", LAYOUTS)
+@pytest.mark.parametrize("bt,m,n,k", [(40, 64, 128, 96), (7, 40, 24, 1575), (9, 16, 33, 70), (13, 50, 70, 40), (256, 16, 64, 33), (61, 40, 100, 9)])
+def test_batches_of_few_tiles(bt, m, n, k, ta, tb):
+    # tiles of all matrices are dealt to the XCDs in one sequence: counts that are and are not multiples of 8, up to one
+    # tile per CU; every matrix its own
+    print(f"gemm split batch {bt}x{m}x{n}x{k} ta={ta} tb={tb}", flush=True)
+    assert split_config(m, n, k, bt) is not None
+    a, b = (I.normal_bf16((bt, *s), 6, i) for i, s in ((1, (k, m) if ta else (m, k)), (2, (n, k) if tb else (k, n))))
+    c = torch.full((bt, m, n), float("nan"), dtype=torch.float32, device=DEV)
+    C.gemm_strided_batched(m, n, k, dev_bf16(a), a.shape[2], m * k, dev_bf16(b), b.shape[2], n * k, c, n, m * n, bt,
+                           trans_a=ta, trans_b=tb)
+    torch.cuda.synchronize()
+    got = host_f32(c)
+    for z in range(bt):
+        assert_bits(got[z], oracle.gemm(a[z], b[z], bool(ta), bool(tb)), f"batch {z}")
