@@ -620,6 +620,19 @@ __global__ __launch_bounds__(CF::NT, CF::OCC * CF::NW / 4) void gemm_mfma_kernel
     }
     return;
   }
+  // A whole tile needs no tests: with them, contractions of up to four chunks had become 1-5% slower than before the
+  // shifted tiles, without 0-14% faster (2048 x 50304 x 64 both transposed 232 before, 240 and 203 us).  The 32x32 shape
+  // beyond 31 chunks has no registers left for a second store loop (2048 x 16384 x 2048 input gradient 1239, 1245 us).
+  if ((V == 16 || MAXL <= 5) && rn == BM && cn == TBN && !g.out_bf16) {
+    float* C = (float*)g.c + z1 * g.sc1 + z2 * g.sc2;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const int64_t i = crow0 + Mfma<V>::orow(v, lane);
+      const int64_t j = ccol0 + Mfma<V>::ocol(v, lane);
+      C[i * g.ldc + j] = r[v];
+    }
+    return;
+  }
 #pragma unroll
   for (int v = 0; v < V; ++v) {
     const int64_t i = crow0 + Mfma<V>::orow(v, lane);
