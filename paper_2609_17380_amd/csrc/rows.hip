@@ -201,11 +201,22 @@ struct RegStage {
 template <int H = 0, int Q>
 __device__ __forceinline__ float reg_row_sum(RegStage& st, const float (&e)[Q][4], int64_t n) {
   const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int q = 0; q < kRegQ; ++q) {
+  auto stage = [&](int q) __attribute__((always_inline)) {
     const int local = 256 * q + 4 * lane;
     const float(&v)[4] = e[H * kRegQ + q];
     *reinterpret_cast<float4*>(&st.t[local >> 5][local & 31]) = make_float4(v[0], v[1], v[2], v[3]);
+  };
+  // short rows leave out the vectors past their end (norm forward of 20000 rows of 16 terms 11.2 -> 9.9 us); with the
+  // test in front of every vector the softmax of 2048 keys took 66 us instead of 59
+  if (n > 256 * (kRegQ - 1)) {
+#pragma unroll
+    for (int q = 0; q < kRegQ; ++q) stage(q);
+  } else {
+#pragma unroll
+    for (int q = 0; q < kRegQ - 1; ++q) {
+      if (256 * q >= n) break;
+      stage(q);
+    }
   }
   __builtin_amdgcn_wave_barrier();
   const int nc = (int)((n + kChunk - 1) / kChunk);
