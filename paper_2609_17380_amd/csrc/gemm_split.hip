@@ -28,11 +28,18 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int SW = 8;   // wavefronts of a workgroup (K ranges per block)
 constexpr int KC = 32;  // chunk length
-// Fold stack of a range (up to 2^11 chunks: 4095 over 2 ranges): register levels, then private memory.  With two
-// register levels the scratch accesses, one dependent round trip per four chunks, doubled a chunk's time.
+// Fold stack of a range: register levels, then private memory.  With two register levels the scratch accesses, one
+// dependent round trip per four chunks, doubled a chunk's time.  Of at most 4095 chunks (the library's 12 levels) a
+// range of RG row groups and KB K blocks holds up to 4096 / (SW / RG * KB), a power of two.
 template <int KB>
 constexpr int kRegLevels = KB == 1 ? 5 : 3;
-constexpr int kMemLevels = 9;
+constexpr int kMaxChunks = 4096;
+template <int RG, int KB>
+constexpr int mem_levels() {
+  int levels = 1;
+  while ((SW / RG * KB << (levels - 1)) < kMaxChunks) ++levels;
+  return levels - kRegLevels<KB>;
+}
 constexpr uint32_t kPadA = 0x8000u, kPadB = 0x3F80u;  // bf16 -0 and 1
 
 // K block of accumulator register v (KB > 1: the instruction's block v / 4 is column block * KB + K block)
@@ -41,9 +48,9 @@ __device__ __forceinline__ constexpr int kblock(int v) { return (v >> 2) % KB; }
 
 // Binary-carry stack over one wavefront's ranges, n[kb] chunks each; a push of local chunk q beyond a block's own
 // chunks leaves that block's entries alone.
-template <int KB>
+template <int KB, int LEVELS>
 struct SplitMem {
-  float s[kMemLevels][16];
+  float s[LEVELS][16];
   __device__ __forceinline__ void push(v16f p, uint32_t c, const bool (&live)[KB]) {
     int L = 0;
     for (; c & 1; c >>= 1, ++L) {
@@ -55,7 +62,8 @@ struct SplitMem {
       if (live[kblock<KB>(v)]) s[L][v] = p[v];
   }
   __device__ __forceinline__ void result(v16f& r, bool (&have)[KB], const uint32_t (&n)[KB], int lev) const {
-    for (int L = 0; L < kMemLevels; ++L, ++lev)
+#pragma unroll 1
+    for (int L = 0; L < LEVELS; ++L, ++lev)
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb)
         if ((n[kb] >> lev) & 1) {
@@ -70,7 +78,8 @@ template <int KB, int R>
 struct SplitFold {
   v16f s;
   SplitFold<KB, R - 1> up;
-  __device__ __forceinline__ void push(const v16f& p, uint32_t c, const bool (&live)[KB], SplitMem<KB>& mem) {
+  template <class Mem>
+  __device__ __forceinline__ void push(const v16f& p, uint32_t c, const bool (&live)[KB], Mem& mem) {
     if (c & 1) {
       up.push(s + p, c >> 1, live, mem);
     } else {
@@ -80,8 +89,9 @@ struct SplitFold {
     }
   }
   // lowest occupied level first, then the others in ascending level order
+  template <class Mem>
   __device__ __forceinline__ void result(v16f& r, bool (&have)[KB], const uint32_t (&n)[KB], int lev,
-                                         const SplitMem<KB>& mem) const {
+                                         const Mem& mem) const {
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
       if ((n[kb] >> lev) & 1) {
@@ -95,11 +105,13 @@ struct SplitFold {
 };
 template <int KB>
 struct SplitFold<KB, 0> {
-  __device__ __forceinline__ void push(const v16f& p, uint32_t c, const bool (&live)[KB], SplitMem<KB>& mem) {
+  template <class Mem>
+  __device__ __forceinline__ void push(const v16f& p, uint32_t c, const bool (&live)[KB], Mem& mem) {
     mem.push(p, c, live);
   }
+  template <class Mem>
   __device__ __forceinline__ void result(v16f& r, bool (&have)[KB], const uint32_t (&n)[KB], int lev,
-                                         const SplitMem<KB>& mem) const {
+                                         const Mem& mem) const {
     mem.result(r, have, n, lev);
   }
 };
@@ -283,7 +295,7 @@ __global__ __launch_bounds__(64 * SW, 2) void gemm_split_kernel(GemmArgs g, uint
     yb = *reinterpret_cast<const v4f*>(fb0 + buf * RBUF + 4 * g4);
   };
   SplitFold<KB, kRegLevels<KB>> fold;
-  SplitMem<KB> mem;
+  SplitMem<KB, mem_levels<RG, KB>()> mem;
   uint32_t pos = 0;  // local chunks pushed
   auto push = [&](const v16f& p) {
     bool live[KB];
