@@ -89,7 +89,8 @@ __device__ __forceinline__ float cexp_mid(float x) {
 }
 __device__ __forceinline__ bool cexp_is_mid(float x) { return x * kLog2e > -125.5f; }
 
-// two finite or infinite, never subnormal values (results of arithmetic: flushed) to bf16, round to nearest even
+// two values that are never subnormal (results of arithmetic: flushed) to bf16, round to nearest even; an infinity stays
+// itself and a NaN a NaN (of unspecified sign and payload, like every NaN that arithmetic passes on)
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   uint32_t r;
   asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(lo), "v"(hi));

@@ -116,8 +116,9 @@ __device__ __forceinline__ void stb4(uint16_t* row, int64_t j, int64_t n, const 
 // Coalesced row reduction for one wavefront.  A segment of 64 chunks (2048 terms) is read coalesced (lane l
 // takes terms 64W q + W l .. + W-1), staged in LDS as padded rows [chunk][33], and lane c then runs chunk
 // c's chain sequentially from LDS; the chunk partials of all segments collect in `parts` and are folded by
-// lane blocks + wave_fold (Algorithm 2).  term(j, f) evaluates terms j .. j+W-1 of the row into f (for
-// W > 1 the row length is a multiple of W, so a vector is either wholly inside the row or wholly past it).
+// lane blocks + wave_fold (Algorithm 2).  term(j, f) evaluates terms j .. j+W-1 of the row into f; it is called for
+// j < n only, and reads nothing at or past n itself (rows of any length: the last vector may be partial, and the chain
+// stops at n whatever f holds there).
 struct WaveStage {
   float t[64][33];
 };
@@ -961,7 +962,6 @@ __global__ __launch_bounds__(NT) void xent_row_kernel(int vocab, const uint16_t*
   __shared__ __attribute__((aligned(16))) float st[SEG][CPS][36];
   extern __shared__ float parts[];
   __shared__ float red[2][NT / 64];
-  __shared__ float total;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, t = threadIdx.x;
   const int64_t row = blockIdx.x;
   const uint16_t* lr = logits + row * vocab;

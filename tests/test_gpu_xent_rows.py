@@ -1,6 +1,7 @@
 """Cross-entropy rows at the edges of the launch rule (vocab 10240, 26624 and 57344), of the 8-wide vectors and of the
 chunks, and with logits far enough below the row's maximum that their exponential is zero: bit-identical to the oracle.
-Infinite logits give the arithmetic's own results (a row of -inf but one target: probability one)."""
+Infinite logits give the arithmetic's own results (a row of -inf but one target: probability one), and rows that hold a
+NaN are NaN."""
 
 import numpy as np
 import pytest
@@ -42,3 +43,30 @@ def test_xent_rows(vocab, z):
     np.testing.assert_array_equal(out[1:-1].reshape(rows, vocab), dl_o)
     np.testing.assert_array_equal(rl.cpu().numpy().view(np.uint32), rl_o.view(np.uint32))
     assert ml.cpu().numpy().view(np.uint32)[0] == np.float32(ml_o).view(np.uint32)
+
+
+@pytest.mark.parametrize("vocab", [9, 1000, 10241, 57344, 57345])
+def test_xent_rows_with_nan(vocab):
+    # a NaN logit (either sign, quiet or not), +inf, and a row of -inf make a row of NaN: a NaN must round to a bf16 NaN,
+    # never to a number or an infinity (which NaN it is, is not specified).  The rows between stay the oracle's bits.
+    rows = 9
+    print(f"xent nan rows vocab={vocab}", flush=True)
+    logits = I.normal_bf16((rows, vocab), 1, I.TENSOR_IDS["logits"], std=2.0)
+    for r, at, bits in ((0, 0, 0x7FC0), (1, vocab - 1, 0xFFC0), (2, vocab // 2, 0x7F81), (3, 1, 0xFFFF), (5, vocab - 2, 0x7F80)):
+        logits[r, at] = bits
+    logits[6, :] = 0xFF80
+    tgt = np.array([0, 1, 2, 1, 0, 0, 0, vocab - 1, 3], np.int32)
+    inv = np.float32(1 / rows)
+    dl_o, rl_o, _ = oracle.xent(logits, tgt, inv)
+    nan_o = (dl_o & 0x7FFF) > 0x7F80
+    assert nan_o[[0, 1, 2, 3, 5, 6]].all() and not nan_o[[4, 7, 8]].any()
+    dl = torch.zeros((rows, vocab), dtype=torch.bfloat16, device=DEV)
+    rl = torch.empty(rows, dtype=torch.float32, device=DEV)
+    C.softmax_xent(C.XENT, rows, vocab, torch.from_numpy(logits.view(np.int16)).view(torch.bfloat16).to(DEV), dl,
+                   targets=torch.from_numpy(tgt).to(DEV), inv_tokens=float(inv), row_loss=rl)
+    torch.cuda.synchronize()
+    out, loss = dl.cpu().view(torch.int16).numpy().view(np.uint16), rl.cpu().numpy()
+    np.testing.assert_array_equal((out & 0x7FFF) > 0x7F80, nan_o)
+    np.testing.assert_array_equal(np.where(nan_o, 0, out), np.where(nan_o, 0, dl_o))
+    np.testing.assert_array_equal(np.isnan(loss), np.isnan(rl_o))
+    np.testing.assert_array_equal(loss[[4, 7, 8]].view(np.uint32), rl_o[[4, 7, 8]].view(np.uint32))
