@@ -197,7 +197,8 @@ __global__ __launch_bounds__(64 * SW, 2) void gemm_split_kernel(GemmArgs g, uint
   constexpr int PFLOATS = SW * 16 * 64;                        // the ranges' results
   __shared__ __attribute__((aligned(16))) float lds[RBUF * NBUF * S > PFLOATS ? RBUF * NBUF * S : PFLOATS];
   // each XCD (every 8th workgroup) takes a contiguous run of the batch's tiles, row tiles fastest, so that its L2 holds
-  // a few column panels or matrices (dealt by matrix, a batch of 40 with 4 tiles each had work for four of the XCDs)
+  // a few column panels or matrices (40 x 64 x 128 x 512, four tiles each: 10.1 us; numbered within each matrix, half
+  // of the XCDs had no work, 19.2)
   const uint32_t at = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
   const uint32_t z = at / tiles, tile = at - z * tiles;
   if (z >= (uint32_t)g.batch) return;

@@ -936,12 +936,12 @@ hipError_t softmax_causal_launch(int64_t rows, int64_t cols, const float* raw, f
 // Cross-entropy, one workgroup of NT threads per row, the row read from memory once: thread t holds the 8 logits
 // 8 (t + NT q) .. + 7 for q < Q.  EXPS keeps the exponentials in registers (one cexp per logit, rows up to 26624);
 // longer rows keep the bf16 logits in 64 or 108 registers, so that two (one) workgroups of 16 wavefronts share a CU,
-// and evaluate cexp again for the output (50304 logits with the exponentials kept: 512 threads 584 us, 1024 threads,
-// one workgroup per CU, 543; logits kept: 531).  The exponentials are staged SEG vectors at a time as chunk rows of 36
+// and evaluate cexp again for the output (50304 logits, one run under a lower clock than the figures below: with the
+// exponentials kept, 512 threads 584 us, 1024 threads, one workgroup per CU, 543; logits kept 531).  The exponentials are staged SEG vectors at a time as chunk rows of 36
 // floats (16-byte stores, and 16-byte reads without bank conflicts), thread c running chunk c's chain.  Rows start at
 // any element (16-byte accesses need no alignment).
 // Bound: vector instructions, about 56 per logit with two cexp of 22 (no range selects where no logit is far enough
-// below the maximum).  8192 x 50304: 750 -> 531 us (3.1 TB/s); 8192 x 50257: 2010 -> 592; 8192 x 20000: 402 -> 206.
+// below the maximum).  8192 x 50304: 742 -> 516 us (3.2 TB/s); 8192 x 50257: 1999 -> 555; 8192 x 20000: 323 -> 203.
 struct __attribute__((packed, aligned(2))) Row8 {
   uint32_t w[4];
 };
